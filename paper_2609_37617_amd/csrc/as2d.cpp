@@ -53,6 +53,8 @@ struct PassBufs {
   float *amax_val = nullptr, *amax_val2 = nullptr, *row_margin = nullptr;
   float *part = nullptr, *pacc = nullptr, *pml = nullptr;
   int *amax_idx = nullptr, *counters = nullptr, *row_tok = nullptr, *row_bad = nullptr, *fin_counters = nullptr;
+  size_t part_elems = 0;                                 // floats of part
+  int n_counters = 0;
   void *xg = nullptr, *attn = nullptr, *hbuf = nullptr;  // activation planes
   long long xg_plane = 0, attn_plane = 0, h_plane = 0;    // offset of the lo plane (bf16), elements
   int part_spans = 0;                                     // span stride of the attention states
@@ -93,7 +95,7 @@ struct as2d_ctx {
   void* audio = nullptr;      // audio rows of the prefill being run
   size_t audio_cap = 0;
   int n_blocks_cap = 0;   // 64-key attention blocks of a full slot
-  int max_rows = 0;
+  int prefill_rows = 0;   // rows of a prefill pass, at most (a multiple of 16)
 
   RowDesc* h_rows = nullptr;
   ReqDesc* h_reqs = nullptr;
@@ -342,6 +344,8 @@ GemmArgs base_args(as2d_ctx* c, const GemmPlan& pl, const uint4* W, int M, const
   a.eps = c->cfg.rms_eps;
   a.part = B.part;
   a.counters = B.counters;
+  a.part_bytes = (long long)B.part_elems * 4;
+  a.n_counters = B.n_counters;
   a.rows = B.d_rows;
   return a;
 }
@@ -354,7 +358,8 @@ float attn_scale(int d) { return (float)(1.4426950408889634 / std::sqrt((double)
 // device descriptors: n_att attention requests (d_reqs[0..n_att)), n_fin
 // finish requests (d_reqs[max_requests..)) covering fin_rows rows;
 // with_head = run the LM head and verification; prefill = a prefill pass
-// (one request, its rows in order).  max_blocks bounds the
+// (one request, its rows in order): its head runs over the last row tile
+// only, whose first row becomes row 0 of the logits and arg-max buffers.  max_blocks bounds the
 // attention key blocks of any request (it sizes the attention grid).
 int launch_pass(as2d_ctx* c, const PassBufs& B, int M, int n_att, int n_fin, int fin_rows, bool with_head,
                 int max_blocks, bool prefill) {
@@ -455,9 +460,11 @@ int launch_pass(as2d_ctx* c, const PassBufs& B, int M, int n_att, int n_fin, int
   }
   if (with_head) {
     {
-      GemmArgs a = base_args(c, c->p_lm, c->lm, M, &B);
-      a.A = B.xg;
+      const int m0 = prefill ? (M - 1) & ~15 : 0;
+      GemmArgs a = base_args(c, c->p_lm, c->lm, M - m0, &B);
+      a.A = (const char*)B.xg + (size_t)m0 * g.hidden * c->es;
       a.a_plane = B.xg_plane;
+      a.sumsq = B.sumsq + (size_t)m0 * (g.hidden / kPairCols);
       a.logits = c->keep_logits ? B.logits : nullptr;
       a.amax_val = B.amax_val;
       a.amax_val2 = B.amax_val2;
@@ -704,8 +711,9 @@ int run_forward(as2d_ctx* c, int M, int n_att, int n_fin, bool with_head, bool v
   if (persistent) HIP_TRY(c, hipMemcpyAsync(&c->h_err, c->perr, sizeof(int), hipMemcpyDeviceToHost, s));
   if (with_head) {
     HIP_TRY(c, hipMemcpyAsync(c->h_out, c->b.d_out, sizeof(StepOut) * n_fin, hipMemcpyDeviceToHost, s));
-    HIP_TRY(c, hipMemcpyAsync(c->h_tok, c->b.row_tok, sizeof(int) * M, hipMemcpyDeviceToHost, s));
-    HIP_TRY(c, hipMemcpyAsync(c->h_margin, c->b.row_margin, sizeof(float) * M, hipMemcpyDeviceToHost, s));
+    const int n_rows = verify_call ? M : (M - 1) % 16 + 1;
+    HIP_TRY(c, hipMemcpyAsync(c->h_tok, c->b.row_tok, sizeof(int) * n_rows, hipMemcpyDeviceToHost, s));
+    HIP_TRY(c, hipMemcpyAsync(c->h_margin, c->b.row_margin, sizeof(float) * n_rows, hipMemcpyDeviceToHost, s));
   }
   HIP_TRY(c, hipStreamSynchronize(s));
   timing_collect(c);
@@ -875,13 +883,14 @@ int commit_verify(as2d_ctx* c, int n, const int32_t* reqs, const int32_t* ks, as
   return AS2D_OK;
 }
 
-// Split-K counters a pass may use: one per workgroup tile (at most one per
-// tile pair on the direct path; on the staged path one per (group of
-// kPairsS pairs, row group), at most kMaxMTiles row groups).
-int split_counter_count(const as2d_ctx* c) {
+// Split-K counters a pass of up to `rows` rows may use: one per workgroup
+// tile (at most one per tile pair on the direct path; on the staged and wide
+// paths one per (group of kPairsS pairs, row group), at most kMaxMTiles and
+// one per two row tiles).
+int split_counter_count(const as2d_ctx* c, int rows) {
   int n = 0;
   for (const GemmPlan* p : {&c->p_qkv, &c->p_o, &c->p_gu, &c->p_down, &c->p_lm})
-    n = std::max({n, p->pairs, (p->pairs / kPairsS) * kMaxMTiles});
+    n = std::max({n, p->pairs, (p->pairs / kPairsS) * std::max(kMaxMTiles, (rows + 31) / 32)});
   return n;
 }
 
@@ -924,7 +933,9 @@ size_t static_layout(const as2d_ctx* c, int n_blocks, char* base, PassBufs* S) {
   S->row_margin = (float*)take(R * 4);
   S->fin_counters = (int*)take((size_t)g.max_requests * 4);
   S->part = (float*)take(part * 4);
-  S->counters = (int*)take((size_t)split_counter_count(c) * 4);
+  S->part_elems = part;
+  S->n_counters = split_counter_count(c, kStaticRows);
+  S->counters = (int*)take((size_t)S->n_counters * 4);
   S->part_spans = (int)((n_blocks + kAttnSpan - 1) / kAttnSpan);
   const size_t spans = (n_blocks + kAttnSpan - 1) / kAttnSpan;
   S->pacc = (float*)take(spans * R * QD * 4);
@@ -1114,23 +1125,26 @@ int as2d_load_weights(const as2d_config* cfg, const void* const* host, int32_t n
   CK(dalloc(c, &c->kc, kv_bytes));
   CK(dalloc(c, &c->vc, kv_bytes));
 
-  // activations and scratch, sized for the largest pass
-  c->max_rows = kMaxRows;   // rows per pass (prefill chunks, fused batches)
+  // activations and scratch, sized for the largest pass: MR rows of a
+  // verification pass, PR of any pass (a prefill of a bf16 model takes up to
+  // kPrefillRows rows at a time)
   const int MR = kMaxRows;
+  c->prefill_rows = c->bf16 ? std::min(kPrefillRows, (g.max_kv_len + 15) / 16 * 16) : MR;
+  const size_t PR = std::max(c->prefill_rows, MR);
   c->n_blocks_cap = (g.max_kv_len + kAttnBlock - 1) / kAttnBlock;
-  CK(dalloc(c, &c->b.x, (size_t)MR * H * 4));
-  CK(dalloc(c, &c->b.q, (size_t)MR * nq * d * 4));
+  CK(dalloc(c, &c->b.x, PR * H * 4));
+  CK(dalloc(c, &c->b.q, PR * nq * d * 4));
   // activation planes: two bf16 planes or one float32 plane, 4 bytes per element either way
-  CK(dalloc(c, &c->b.xg, (size_t)MR * H * 4));
-  CK(dalloc(c, &c->b.attn, (size_t)MR * nq * d * 4));
-  CK(dalloc(c, &c->b.hbuf, (size_t)MR * F * 4));
+  CK(dalloc(c, &c->b.xg, PR * H * 4));
+  CK(dalloc(c, &c->b.attn, PR * nq * d * 4));
+  CK(dalloc(c, &c->b.hbuf, PR * F * 4));
   if (c->bf16) {
-    c->b.xg_plane = (long long)MR * H;
-    c->b.attn_plane = (long long)MR * nq * d;
-    c->b.h_plane = (long long)MR * F;
+    c->b.xg_plane = (long long)PR * H;
+    c->b.attn_plane = (long long)PR * nq * d;
+    c->b.h_plane = (long long)PR * F;
   }
   CK(dalloc(c, &c->b.logits, (size_t)MR * V * 4));
-  CK(dalloc(c, &c->b.sumsq, (size_t)(H / kPairCols) * MR * 4));
+  CK(dalloc(c, &c->b.sumsq, (H / kPairCols) * PR * 4));
   CK(dalloc(c, &c->b.amax_val, (size_t)(V / kPairCols) * MR * 4));
   CK(dalloc(c, &c->b.amax_val2, (size_t)(V / kPairCols) * MR * 4));
   CK(dalloc(c, &c->b.row_margin, (size_t)MR * 4));
@@ -1139,13 +1153,16 @@ int as2d_load_weights(const as2d_config* cfg, const void* const* host, int32_t n
   CK(dalloc(c, &c->b.row_bad, (size_t)MR * 4));
   CK(dalloc(c, &c->b.fin_counters, (size_t)g.max_requests * 4));
   HIP_TRY(c, hipMemsetAsync(c->b.fin_counters, 0, (size_t)g.max_requests * 4, c->stream));
-  size_t part_elems = 0;
+  // split-K partials: of whole verification passes, and on the wide path of
+  // whole tiles; smaller units of the wide path take up to 128 MiB
+  size_t part_elems = c->bf16 ? 32u << 20 : 0;
   for (const GemmPlan* p : {&c->p_qkv, &c->p_o, &c->p_gu, &c->p_down, &c->p_lm})
-    if (p->KS > 1) part_elems = std::max(part_elems, (size_t)p->KS * MR * p->N);
+    if (p->KS > 1) part_elems = std::max({part_elems, (size_t)p->KS * MR * p->N, wide_scratch_floats(p->N, (int)PR)});
   CK(dalloc(c, &c->b.part, part_elems * 4));
-  const int n_cnt = split_counter_count(c);
-  CK(dalloc(c, &c->b.counters, (size_t)n_cnt * 4));
-  HIP_TRY(c, hipMemsetAsync(c->b.counters, 0, (size_t)n_cnt * 4, c->stream));
+  c->b.part_elems = part_elems;
+  c->b.n_counters = split_counter_count(c, (int)PR);
+  CK(dalloc(c, &c->b.counters, (size_t)c->b.n_counters * 4));
+  HIP_TRY(c, hipMemsetAsync(c->b.counters, 0, (size_t)c->b.n_counters * 4, c->stream));
   HIP_TRY(c, prepare_kernels());
   {
     // the static scratch of as2d_verify_static: its address on this device
@@ -1193,7 +1210,7 @@ int as2d_load_weights(const as2d_config* cfg, const void* const* host, int32_t n
   CK(dalloc(c, &c->b.pml, spans_cap * MR * nq * 2 * 4));
   CK(dalloc(c, &c->b.attn_cnt, (size_t)g.max_requests * nq * 2 * 4));
   HIP_TRY(c, hipMemsetAsync(c->b.attn_cnt, 0, (size_t)g.max_requests * nq * 2 * 4, c->stream));
-  CK(dalloc(c, &c->b.d_rows, sizeof(RowDesc) * MR));
+  CK(dalloc(c, &c->b.d_rows, sizeof(RowDesc) * PR));
   CK(dalloc(c, &c->b.d_reqs, sizeof(ReqDesc) * 2 * g.max_requests));
   CK(dalloc(c, &c->b.d_out, sizeof(StepOut) * g.max_requests));
 
@@ -1210,7 +1227,7 @@ int as2d_load_weights(const as2d_config* cfg, const void* const* host, int32_t n
     CK(dalloc(c, &c->rope_cs, cs.size() * 4));
     HIP_TRY(c, hipMemcpy(c->rope_cs, cs.data(), cs.size() * 4, hipMemcpyHostToDevice));
   }
-  if (hipHostMalloc((void**)&c->h_rows, sizeof(RowDesc) * MR, 0) != hipSuccess ||
+  if (hipHostMalloc((void**)&c->h_rows, sizeof(RowDesc) * PR, 0) != hipSuccess ||
       hipHostMalloc((void**)&c->h_reqs, sizeof(ReqDesc) * 2 * g.max_requests, 0) != hipSuccess ||
       hipHostMalloc((void**)&c->h_out, sizeof(StepOut) * g.max_requests, 0) != hipSuccess ||
       hipHostMalloc((void**)&c->h_tok, sizeof(int) * MR, 0) != hipSuccess ||
@@ -1260,7 +1277,9 @@ int as2d_prefill_kv(as2d_ctx* c, int32_t req, const void* audio, int32_t n_audio
     }
     HIP_TRY(c, hipMemcpyAsync(c->audio, audio, bytes, hipMemcpyHostToDevice, c->stream));
   }
-  const int chunk = c->max_rows;
+  // passes of about the same number of whole row tiles
+  const int passes = (total + c->prefill_rows - 1) / c->prefill_rows;
+  const int chunk = ((total + passes - 1) / passes + 15) / 16 * 16;
   const int mr = g.max_requests;
   for (int r0 = 0; r0 < total; r0 += chunk) {
     const int M = std::min(chunk, total - r0);
@@ -1276,12 +1295,12 @@ int as2d_prefill_kv(as2d_ctx* c, int32_t req, const void* audio, int32_t n_audio
     }
     c->h_reqs[0] = ReqDesc{0, M, r0, req};
     const bool last = r0 + M == total;
-    c->h_reqs[mr] = ReqDesc{M - 1, 1, r0 + M - 1, req};
+    c->h_reqs[mr] = ReqDesc{(M - 1) % 16, 1, r0 + M - 1, req};   // the head's rows: launch_pass
     if ((rc = run_forward(c, M, 1, 1, last))) return rc;
     if (last) {
       if (c->h_out[0].nan_flag) return fail(c, AS2D_ENUMERIC, "prefill: non-finite logits");
       st.root = c->h_out[0].correction;
-      st.last_row_start = M - 1;
+      st.last_row_start = (M - 1) % 16;
       st.last_rows = 1;
       st.last_logits = c->keep_logits;
     }
@@ -1324,7 +1343,7 @@ int as2d_verify_static(as2d_ctx* c, int32_t req, const int32_t* cands, int32_t k
   HIP_TRY(c, hipMemcpyAsync(S.d_rows, c->h_rows, sizeof(RowDesc) * M, hipMemcpyHostToDevice, s));
   HIP_TRY(c, hipMemcpyAsync(S.d_reqs, c->h_reqs, sizeof(ReqDesc) * 2 * mr, hipMemcpyHostToDevice, s));
   // the array keeps the last call's contents: counters must start at zero
-  HIP_TRY(c, launch_fill_zero(S.counters, split_counter_count(c), s));
+  HIP_TRY(c, launch_fill_zero(S.counters, S.n_counters, s));
   HIP_TRY(c, launch_fill_zero(S.fin_counters, mr, s));
   HIP_TRY(c, launch_fill_zero(S.attn_cnt, mr * g.n_q_heads * 2, s));
   const int timing = c->timing;   // no event bracketing here (events are created on first use)

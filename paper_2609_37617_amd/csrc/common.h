@@ -86,6 +86,10 @@ __device__ __forceinline__ float2 ld_coherent2(__amdgpu_buffer_rsrc_t r, uint32_
   const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, kCPolSC1);
   return make_float2(__uint_as_float(v[0]), __uint_as_float(v[1]));
 }
+// The store that matches ld_coherent4: 16 bytes past this XCD's L2.
+__device__ __forceinline__ void st_coherent4(__amdgpu_buffer_rsrc_t r, uint32_t off, f4 v) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, off, 0, kCPolSC1);
+}
 
 // Index of element (m, k) of an activation operand with K columns in MFMA
 // fragment order: one block of 16 rows x KE elements (one k-step of one
@@ -115,6 +119,34 @@ template <bool BF, bool COH> __device__ __forceinline__ void store_act(void* bas
     st<COH>(b + i + plane, f2bf(v - bf2f(hi)));
   } else {
     st<COH>(static_cast<float*>(base) + i, v);
+  }
+}
+
+// The (hi, lo) bf16 pair of the product a b: hi from the rounded product, lo
+// from the exact one.
+struct BfPair {
+  uint16_t hi, lo;
+};
+__device__ __forceinline__ BfPair split_mul(float a, float b) {
+#pragma clang fp contract(off)
+  const uint16_t hi = f2bf(a * b);
+  return BfPair{hi, f2bf(__builtin_fmaf(a, b, -bf2f(hi)))};
+}
+// The same of a value.
+__device__ __forceinline__ BfPair split_val(float v) {
+  const uint16_t hi = f2bf(v);
+  return BfPair{hi, f2bf(v - bf2f(hi))};
+}
+// Activation planes: the product a b at element i.
+template <bool BF, bool COH>
+__device__ __forceinline__ void store_act_mul(void* base, long long plane, size_t i, float a, float b) {
+  if constexpr (BF) {
+    uint16_t* o = static_cast<uint16_t*>(base);
+    const BfPair v = split_mul(a, b);
+    st<COH>(o + i, v.hi);
+    st<COH>(o + i + plane, v.lo);
+  } else {
+    st<COH>(static_cast<float*>(base) + i, a * b);
   }
 }
 
@@ -277,6 +309,24 @@ __device__ __forceinline__ float lane_value(float v, int lane) {
 __device__ __forceinline__ float half_sum(float v) {
   return half_reduce(v, [](float a, float b) { return a + b; });
 }
+// Sum of squares of a half-wave's values: half_sum of the squares, whose
+// first step takes a lane's own square unrounded (a fused multiply-add).  As
+// lane 0 of the half sees it, eight consecutive values add as sumsq8 does,
+// and the groups of eight in a balanced tree.
+__device__ __forceinline__ float half_sumsq(float e) {
+#pragma clang fp contract(off)
+  float v = __builtin_fmaf(e, e, dpp_get<kDppXor1>(e * e));
+  v = v + dpp_get<kDppXor2>(v);
+  v = v + dpp_get<kDppHalfMirror>(v);
+  v = v + dpp_get<kDppMirror>(v);
+  return v + swizzle_xor16(v);
+}
+__device__ __forceinline__ float sumsq8(const float (&e)[8]) {
+#pragma clang fp contract(off)
+  const float a = __builtin_fmaf(e[0], e[0], e[1] * e[1]) + __builtin_fmaf(e[2], e[2], e[3] * e[3]);
+  const float b = __builtin_fmaf(e[7], e[7], e[6] * e[6]) + __builtin_fmaf(e[5], e[5], e[4] * e[4]);
+  return a + b;
+}
 __device__ __forceinline__ float wave_sum(float v) {
   v = half_sum(v);
   return lane_value(v, 0) + lane_value(v, 32);
@@ -302,6 +352,14 @@ __device__ __forceinline__ void half_argmax(float& v, int& i) {
     int oi = __shfl_xor(i, o);
     if (ov > v || (ov == v && oi < i)) { v = ov; i = oi; }
   }
+}
+
+// Workgroups are dealt to the 8 XCDs round-robin by linear index.  The
+// index v of the work a block takes: XCD j's blocks take one contiguous
+// range of v (the first n % 8 XCDs one more each), in dispatch order.
+__device__ __forceinline__ int xcd_contiguous(int b, int n) {
+  const int per = n >> 3, rem = n & 7, j = b & 7, slot = b >> 3;
+  return j < rem ? j * (per + 1) + slot : rem * (per + 1) + (j - rem) * per + slot;
 }
 
 // GEMM tile constants

@@ -26,7 +26,8 @@ constexpr int kWaves = 4;               // waves per workgroup
 constexpr int kPairCols = 32;           // columns of a tile pair
 constexpr int kMaxSlices = 16;          // ordered partial sums per k-split, at most
 constexpr int kPairsS = kWaves;         // tile pairs per workgroup, staged path
-constexpr int kMaxMTiles = 9;           // up to 144 rows per forward pass
+constexpr int kMaxMTiles = 9;           // up to 144 rows per verification pass (and float32 prefill pass)
+constexpr int kPrefillRows = 2048;      // rows per prefill pass of bf16 models
 constexpr int kMaxRows = kMaxMTiles * 16;
 constexpr int kDirectMT = 2;            // row tiles of the direct path (up to 32 rows)
 constexpr int kStepRows = kDirectMT * 16;  // rows of a persistent-kernel pass
@@ -77,6 +78,7 @@ struct GemmArgs {
   int G;                 // balanced direct path: workgroups sharing the units (0: one unit
                          // group per workgroup)
   int M, MT;
+  int RB, CB, spu;       // wide path: row blocks, column blocks, slices per unit
   int rg_grid;           // staged path with row groups: row groups of 3, 2 tiles are
                          // used only if their grid reaches rg_grid workgroups (else 1 tile)
   // A operand: activation planes [kMaxRows][K].  For A_NORM the planes
@@ -90,6 +92,8 @@ struct GemmArgs {
   // split-K scratch
   float* part;           // [KS][M][N]
   int* counters;         // one per workgroup tile, zero between launches
+  long long part_bytes;  // sizes of the two (wide path)
+  int n_counters;
   // epilogue
   const RowDesc* rows;
   const float* bias;     // EPI_QKV (may be null)
@@ -217,6 +221,13 @@ hipError_t launch_embed(bool bf16, const RowDesc* rows, int M, const void* embed
                         int H, const float* gain, float* x, float* sumsq, void* xg, long long xg_plane,
                         hipStream_t s);
 hipError_t launch_gemm(bool bf16, int amode, int epi, const GemmArgs& a, hipStream_t s);
+// The wide path of bf16 models (wide.hip): passes of more than kDirectMT row
+// tiles; a.part_bytes and a.n_counters bound the units it can split tiles
+// into.  wide_scratch_floats: what whole tiles of an N-column matrix with
+// k-splits need for passes of `rows` rows.
+hipError_t launch_wide(int amode, int epi, const GemmArgs& a, hipStream_t s);
+size_t wide_scratch_floats(int N, int rows);
+hipError_t prepare_wide();
 int step_lds_bytes(int MT, int head_dim, int hidden);
 // Slice length of the register-resident balanced variant for a gate/up
 // plan (KS, KT) with one row tile, or 0: the persistent kernel to launch.
@@ -227,7 +238,7 @@ hipError_t launch_step(bool bf16, int MT, int head_dim, int sl, const StepArgs& 
 // Attention over n_reqs requests (attn.h).  Verification passes (rows of a
 // request <= 32): max_blocks bounds the 64-key blocks of any request and
 // sizes the grid (any value covers every cache length; the grid is at most
-// kAttnGrid workgroups).  prefill: one request of up to kMaxRows rows.
+// kAttnGrid workgroups).  prefill: one request, its rows in order.
 hipError_t launch_attention(bool bf16, const AttnArgs& a, int n_reqs, int max_blocks, bool prefill, hipStream_t s);
 // n_rows = sum of the requests' W; counters: one per request, zero between launches.
 // Writes each verified row's greedy token, non-finite flag and top-2 margin.

@@ -104,9 +104,10 @@ hipError_t launch_embed(bool bf16, const RowDesc* rows, int M, const void* embed
 // each k-step's 1 KiB weight tiles (fully coalesced, non-temporal) and the
 // activation fragments issued 2 to 4 k-steps ahead of their use.  The
 // streaming must reach every compute unit (each keeps a bounded amount of
-// memory traffic in flight), so narrow matrices are split along k.  More rows
-// (staged path): one workgroup per (4 or 8 tile pairs, k-split, row group),
-// activations staged through LDS.  Both paths add every element in the same
+// memory traffic in flight), so narrow matrices are split along k.  More rows:
+// the wide path (wide.h) for bf16 models; the staged path for float32 models,
+// one workgroup per (4 or 8 tile pairs, k-split, row group), activations
+// staged through LDS.  All paths add every element in the same
 // order, so a row's result does not depend on M.  With KS > 1 each split writes a
 // float32 partial and the last workgroup of the tile (device-scope
 // counter) sums the partials in split order and runs the fused epilogue.
@@ -177,14 +178,6 @@ static hipError_t launch_range(const GemmArgs& a, hipStream_t s) {
 // compute units idle.
 constexpr int kStagedGroupMT = 3;
 
-// Workgroups are dealt to the 8 XCDs round-robin by linear index.  The
-// index v of the work a block takes: XCD j's blocks take one contiguous
-// range of v (the first n % 8 XCDs one more each), in dispatch order.
-__device__ __forceinline__ int xcd_contiguous(int b, int n) {
-  const int per = n >> 3, rem = n & 7, j = b & 7, slot = b >> 3;
-  return j < rem ? j * (per + 1) + slot : rem * (per + 1) + (j - rem) * per + slot;
-}
-
 // Staged path: work item v = (pair group, split, row group), the row group
 // fastest; RG row groups of MT row tiles each (RG = 1: all the pass's rows).
 // With row groups, the RG blocks of one (pair group, split) run on one XCD
@@ -206,22 +199,10 @@ __global__ __launch_bounds__(256, NPW > 1 ? 2 : MT <= kStagedGroupMT ? 4 : 1) vo
                                                                         rg * MT, group * RG + rg);
 }
 
-template <bool BF, int AM, int EPI>
-static hipError_t gemm_dispatch(const GemmArgs& a, hipStream_t s) {
+template <int AM, int EPI>
+static hipError_t launch_staged(const GemmArgs& a, hipStream_t s) {
+  constexpr bool BF = false;
   const int pairs = a.N / kPairCols;
-  if (a.MT <= kDirectMT && a.G > 0) return launch_range<BF, AM, EPI>(a, s);
-  if (a.MT <= kDirectMT) {
-    if ((a.np != 1 && (a.np != 2 || pairs % 2)) || a.ns < kWaves || a.ns > kMaxSlices || a.ns % kWaves)
-      return hipErrorInvalidValue;
-    if (a.MT == 1) {
-      if (a.np == 1) launch_direct<BF, 1, 1, kWaves, AM, EPI>(a, s);
-      else launch_direct<BF, 1, 2, kWaves, AM, EPI>(a, s);
-    } else {
-      if (a.np == 1) launch_direct<BF, 2, 1, kWaves, AM, EPI>(a, s);
-      else launch_direct<BF, 2, 2, kWaves, AM, EPI>(a, s);
-    }
-    return hipGetLastError();
-  }
   if (pairs % kPairsS) return hipErrorInvalidValue;
   const int base = (pairs / kPairsS) * a.KS;
   // matrices with fewer than two workgroups per compute unit: row groups of
@@ -256,6 +237,29 @@ static hipError_t gemm_dispatch(const GemmArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <bool BF, int AM, int EPI>
+static hipError_t gemm_dispatch(const GemmArgs& a, hipStream_t s) {
+  const int pairs = a.N / kPairCols;
+  if (a.MT <= kDirectMT && a.G > 0) return launch_range<BF, AM, EPI>(a, s);
+  if (a.MT <= kDirectMT) {
+    if ((a.np != 1 && (a.np != 2 || pairs % 2)) || a.ns < kWaves || a.ns > kMaxSlices || a.ns % kWaves)
+      return hipErrorInvalidValue;
+    if (a.MT == 1) {
+      if (a.np == 1) launch_direct<BF, 1, 1, kWaves, AM, EPI>(a, s);
+      else launch_direct<BF, 1, 2, kWaves, AM, EPI>(a, s);
+    } else {
+      if (a.np == 1) launch_direct<BF, 2, 1, kWaves, AM, EPI>(a, s);
+      else launch_direct<BF, 2, 2, kWaves, AM, EPI>(a, s);
+    }
+    return hipGetLastError();
+  }
+  if constexpr (BF) {
+    return launch_wide(AM, EPI, a, s);
+  } else {
+    return launch_staged<AM, EPI>(a, s);
+  }
+}
+
 hipError_t launch_gemm(bool bf16, int amode, int epi, const GemmArgs& a, hipStream_t s) {
 #define AS2D_G(bf, am, ep) \
   if (bf16 == bf && amode == am && epi == ep) return gemm_dispatch<bf, am, ep>(a, s);
@@ -281,7 +285,7 @@ hipError_t launch_gemm(bool bf16, int amode, int epi, const GemmArgs& a, hipStre
 // the block to finish (one quarter wave per row and head), else by
 // attn_merge_kernel (one wave per row and head).
 //
-// Prefill passes (one request, up to 144 rows): one workgroup per (query
+// Prefill passes (one request): one workgroup per (query
 // head, 16 rows) walks the spans in ascending order and merges them as it
 // goes, with the same arithmetic, so no partials go through memory.
 
@@ -571,14 +575,14 @@ static hipError_t prepare_range() {
   return e;
 }
 
-template <bool BF, int AM, int EPI>
+template <int AM, int EPI>
 static hipError_t prepare_staged() {
   hipError_t e = hipSuccess;
   auto allow = [&](const void* k, int bytes) {
     if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
   };
 #define AS2D_S(mt) \
-  allow(reinterpret_cast<const void*>(&gemm_staged_kernel<BF, mt, AM, EPI>), gemm_staged_lds_bytes<BF, mt>());
+  allow(reinterpret_cast<const void*>(&gemm_staged_kernel<false, mt, AM, EPI>), gemm_staged_lds_bytes<false, mt>());
   AS2D_S(1) AS2D_S(2) AS2D_S(3) AS2D_S(4) AS2D_S(5) AS2D_S(6) AS2D_S(7) AS2D_S(8) AS2D_S(9)
 #undef AS2D_S
   return e;
@@ -604,12 +608,13 @@ hipError_t prepare_kernels() {
   if (e == hipSuccess) e = prepare_attention<false, 64>();
 #define AS2D_P(bf, am, ep) \
   if (e == hipSuccess) e = prepare_range<bf, am, ep>(); \
-  if (e == hipSuccess) e = prepare_staged<bf, am, ep>();
+  if (e == hipSuccess && !bf) e = prepare_staged<am, ep>();
   AS2D_P(true, A_NORM, EPI_QKV) AS2D_P(true, A_PLAIN, EPI_RESID) AS2D_P(true, A_NORM, EPI_SWIGLU)
   AS2D_P(true, A_NORM, EPI_ARGMAX) AS2D_P(true, A_PLAIN, EPI_DOWN)
   AS2D_P(false, A_NORM, EPI_QKV) AS2D_P(false, A_PLAIN, EPI_RESID) AS2D_P(false, A_NORM, EPI_SWIGLU)
   AS2D_P(false, A_NORM, EPI_ARGMAX) AS2D_P(false, A_PLAIN, EPI_DOWN)
 #undef AS2D_P
+  if (e == hipSuccess) e = prepare_wide();
   return e;
 }
 

@@ -52,7 +52,7 @@ __device__ __forceinline__ void embed_row(const RowDesc* __restrict__ rows, int 
 #pragma unroll
       for (int t = 0; t < kPer; ++t) {
         st<COH>(x + (size_t)m * H + c0 + t, v[ps][t]);
-        store_act<BF, COH>(xg, xg_plane, frag_index<BF>(m, c0 + t, H), v[ps][t] * gain[c0 + t]);
+        store_act_mul<BF, COH>(xg, xg_plane, frag_index<BF>(m, c0 + t, H), v[ps][t], gain[c0 + t]);
         srow[c0 + t] = v[ps][t];
       }
     }
@@ -64,9 +64,19 @@ __device__ __forceinline__ void embed_row(const RowDesc* __restrict__ rows, int 
   for (int u0 = wave * 2; u0 < n_pairs; u0 += 8) {
     const int g = u0 + (lane >> 5);
     const float e = g < n_pairs ? srow[g * kPairCols + (lane & 31)] : 0.0f;
-    const float s = half_sum(e * e);
+    const float s = half_sumsq(e);
     if ((lane & 31) == 0 && g < n_pairs) st<COH>(sumsq + (size_t)m * n_pairs + g, s);
   }
+}
+
+// x sigmoid(x), the gate's activation.
+__device__ __forceinline__ float silu(float x) { return x / (1.0f + expf(-x)); }
+
+// A dimension of a rotated pair: v cos + partner sin (partner negated by the
+// caller for the pair's first half).
+__device__ __forceinline__ float rope(float v, float partner, float cs, float sn) {
+#pragma clang fp contract(off)
+  return __builtin_fmaf(v, cs, partner * sn);
 }
 
 // ---------------------------------------------------------------------------
@@ -92,7 +102,7 @@ __device__ __forceinline__ void epilogue_rows(const GemmArgs& p, float* F, int f
       const size_t o = (size_t)m * N + n;
       const float v = ldg(p.x + o) + F[(m - r0) * fs + c];
       st<COH>(p.x_out + o, v);
-      store_act<BF, COH>(p.out, p.out_plane, frag_index<BF>(m, n, N), v * ldg(p.gain_next + n));
+      store_act_mul<BF, COH>(p.out, p.out_plane, frag_index<BF>(m, n, N), v, ldg(p.gain_next + n));
       F[(m - r0) * fs + c] = v;
     }
     lds_sync();
@@ -101,7 +111,7 @@ __device__ __forceinline__ void epilogue_rows(const GemmArgs& p, float* F, int f
       const bool ok = u < units;
       const int m = ok ? r0 + u / np : r0, pp = u % np;
       const float e = ok ? F[(m - r0) * fs + pp * kPairCols + (lane & 31)] : 0.0f;
-      const float s = half_sum(e * e);
+      const float s = half_sumsq(e);
       if ((lane & 31) == 0 && ok) st<COH>(p.sumsq_out + (size_t)m * (N / kPairCols) + pair0 + pp, s);
     }
   } else if constexpr (EPI == EPI_SWIGLU) {
@@ -111,8 +121,7 @@ __device__ __forceinline__ void epilogue_rows(const GemmArgs& p, float* F, int f
       const int m = r0 + idx / (np * 16), r = idx % (np * 16);
       const int pp = r >> 4, c = r & 15;
       const float g = F[(m - r0) * fs + pp * kPairCols + c], u = F[(m - r0) * fs + pp * kPairCols + 16 + c];
-      store_act<BF, COH>(p.out, p.out_plane, frag_index<BF>(m, (pair0 + pp) * 16 + c, F2),
-                         g / (1.0f + expf(-g)) * u);
+      store_act_mul<BF, COH>(p.out, p.out_plane, frag_index<BF>(m, (pair0 + pp) * 16 + c, F2), silu(g), u);
     }
   } else if constexpr (EPI == EPI_QKV) {
     // PACK_ROPE_PAIRS: pair q of a head holds dims 16 q + c (tile 0) and
@@ -133,7 +142,7 @@ __device__ __forceinline__ void epilogue_rows(const GemmArgs& p, float* F, int f
         const float partner = Fr[c ^ 16] + (p.bias ? ldg(p.bias + pn) : 0.0f);
         const float cs = ldg(p.rope_cs + ((size_t)rd.pos * half + i) * 2);
         const float sn = ldg(p.rope_cs + ((size_t)rd.pos * half + i) * 2 + 1);
-        v = j == 0 ? v * cs - partner * sn : v * cs + partner * sn;
+        v = rope(v, j == 0 ? -partner : partner, cs, sn);
         if (head < p.n_q) {
           st<COH>(p.q_out + (size_t)m * p.n_q * d + n, v);
         } else {
@@ -846,7 +855,8 @@ __device__ __forceinline__ void gemm_range_direct_ra(const GemmArgs& p, int M, u
   range_finish<BF, AM, EPI, COH>(p, M, F, fs, u0, nu, s_scale, s_flags);
 }
 
-// Staged path (more than kDirectMT row tiles): a workgroup owns kPairsS NPW
+// Staged path (float32 models, more than kDirectMT row tiles; bf16 models:
+// wide.h): a workgroup owns kPairsS NPW
 // tile pairs (NPW per wave) of one split, for row tiles [mt0, mt0 + MT);
 // each wave keeps its slices apart in registers (running sum S).  The
 // split's slices are cut into chunks of at most CK k-steps; a chunk's
