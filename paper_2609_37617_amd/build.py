@@ -4,7 +4,7 @@ import subprocess
 import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-SRC = [os.path.join(HERE, "csrc", f) for f in ("kernels.hip", "wide.hip", "step.hip", "static_scratch.hip", "as2d.cpp", "cbuf.cpp",
+SRC = [os.path.join(HERE, "csrc", f) for f in ("kernels.hip", "wide.hip", "attn_prefill.hip", "step.hip", "static_scratch.hip", "as2d.cpp", "cbuf.cpp",
                                                     "decoupled.cpp")]
 LIB = os.path.join(HERE, "libas2d.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -19,6 +19,12 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 // bf16 nearest to f, ties to even (one v_cvt_pk_bf16_f32 on gfx950; NaN stays NaN).
 __device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
+// Two of them, a in the low half.
+__device__ __forceinline__ uint32_t f2bf2(float a, float b) {
+  typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+  typedef float fp2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(fp2{a, b}, bf2));
+}
 __device__ __forceinline__ float bf2f(uint32_t b) { return __uint_as_float(b << 16); }
 
 template <bool BF> struct ET;

@@ -27,7 +27,7 @@ constexpr int kPairCols = 32;           // columns of a tile pair
 constexpr int kMaxSlices = 16;          // ordered partial sums per k-split, at most
 constexpr int kPairsS = kWaves;         // tile pairs per workgroup, staged path
 constexpr int kMaxMTiles = 9;           // up to 144 rows per verification pass (and float32 prefill pass)
-constexpr int kPrefillRows = 2048;      // rows per prefill pass of bf16 models
+constexpr int kPrefillRows = 8192;      // rows per prefill pass of bf16 models
 constexpr int kMaxRows = kMaxMTiles * 16;
 constexpr int kDirectMT = 2;            // row tiles of the direct path (up to 32 rows)
 constexpr int kStepRows = kDirectMT * 16;  // rows of a persistent-kernel pass
@@ -240,6 +240,9 @@ hipError_t launch_step(bool bf16, int MT, int head_dim, int sl, const StepArgs& 
 // sizes the grid (any value covers every cache length; the grid is at most
 // kAttnGrid workgroups).  prefill: one request, its rows in order.
 hipError_t launch_attention(bool bf16, const AttnArgs& a, int n_reqs, int max_blocks, bool prefill, hipStream_t s);
+// The prefill pass of a bf16 model (attn_prefill.hip): one request of a.M rows.
+hipError_t launch_attn_prefill(const AttnArgs& a, hipStream_t s);
+hipError_t prepare_attn_prefill();
 // n_rows = sum of the requests' W; counters: one per request, zero between launches.
 // Writes each verified row's greedy token, non-finite flag and top-2 margin.
 hipError_t launch_finish(const RowDesc* rows, const ReqDesc* reqs, int n_reqs, int n_rows,

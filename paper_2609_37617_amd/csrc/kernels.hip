@@ -537,7 +537,8 @@ static hipError_t attn_dispatch(const AttnArgs& a, int n_reqs, int max_blocks, b
   if (max_blocks > kMaxBlocks || n_reqs < 1) return hipErrorInvalidValue;
   if (prefill) {
     if (n_reqs != 1) return hipErrorInvalidValue;
-    attn_prefill_kernel<BF, D><<<dim3(a.n_q, (a.M + 15) / 16), 512, attn_prefill_lds_bytes<BF, D>(), s>>>(a);
+    if constexpr (BF) return launch_attn_prefill(a, s);
+    else attn_prefill_kernel<BF, D><<<dim3(a.n_q, (a.M + 15) / 16), 512, attn_prefill_lds_bytes<BF, D>(), s>>>(a);
     return hipGetLastError();
   }
   // items of one-tile blocks at the slot capacity, from the most rows a
@@ -595,8 +596,9 @@ template <bool BF, int D>
 static hipError_t prepare_attention() {
   auto allow = [](const void* k, int bytes) { return hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes); };
   hipError_t e = allow(reinterpret_cast<const void*>(&attn_group_kernel<BF, D>), attn_span_lds_bytes<BF, D, 2>());
-  if (e == hipSuccess)
-    e = allow(reinterpret_cast<const void*>(&attn_prefill_kernel<BF, D>), attn_prefill_lds_bytes<BF, D>());
+  if constexpr (!BF)
+    if (e == hipSuccess)
+      e = allow(reinterpret_cast<const void*>(&attn_prefill_kernel<BF, D>), attn_prefill_lds_bytes<BF, D>());
   return e;
 }
 
@@ -615,6 +617,7 @@ hipError_t prepare_kernels() {
   AS2D_P(false, A_NORM, EPI_ARGMAX) AS2D_P(false, A_PLAIN, EPI_DOWN)
 #undef AS2D_P
   if (e == hipSuccess) e = prepare_wide();
+  if (e == hipSuccess) e = prepare_attn_prefill();
   return e;
 }
 
