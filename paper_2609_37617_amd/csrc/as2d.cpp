@@ -236,9 +236,12 @@ void set_grid(GemmPlan& p, int cus) {
 // split count with the least estimated time of the busiest workgroup,
 // i.e. units per workgroup x the longest slice of a split (in k-steps),
 // plus, with k-splits, `split_cost` k-steps for the fixup phase and
-// `per_split` k-steps for each split it reads (measured on the 7B shape:
-// 16 and 5 put QKV at 3 splits, O and down at 2, gate/up and the LM head
-// at 1, the fastest of the sweep).  Every split needs kWaves k-steps (one
+// `per_split` k-steps for each split it reads (48 and 5, from sweeps of the
+// split counts at 1 to 17 rows: 7B shape QKV 1 split 12.9 us against 15.7
+// with 3, O 11.7 either way with 1 or 2, down 29.1 with 2 against 42.3 and
+// 36.3 with 1 and 3; 3B shape QKV and O 1 split, 7.8 and 7.3 us against 9.3
+// and 8.4 with 3 and 4, down 14.3 with 4 against 14.8 with 3; 0.5B shape
+// down 8.6 with 5).  Every split needs kWaves k-steps (one
 // per slice).  A shape with no such split count keeps the plan `p` (G = 0).
 GemmPlan balance_plan(GemmPlan p, int cus, int split_cost, int per_split, int ks_override) {
   constexpr int kNominalCUs = 256;
@@ -1052,7 +1055,8 @@ int as2d_load_weights(const as2d_config* cfg, const void* const* host, int32_t n
       fail(c, AS2D_EHIP, "as2d_load_weights: device query");
       return give_up(AS2D_EHIP);
     }
-    const int sc = env_int("AS2D_SPLIT_COST", 16), ps = env_int("AS2D_SPLIT_COST_PER", 5);
+    // float32 models keep more splits: their sums are the results' precision
+    const int sc = env_int("AS2D_SPLIT_COST", c->bf16 ? 48 : 16), ps = env_int("AS2D_SPLIT_COST_PER", 5);
     if (bal & 1) c->p_qkv = balance_plan(c->p_qkv, cus, sc, ps, ks_qkv);
     if (bal & 2) c->p_o = balance_plan(c->p_o, cus, sc, ps, ks_o);
     if (bal & 4) c->p_gu = balance_plan(c->p_gu, cus, sc, ps, ks_gu);

@@ -625,10 +625,198 @@ __device__ __forceinline__ void range_close(float* R, float* F, int fs, int j, i
   }
 }
 
+// Epilogue of a unit's 32 columns for EPI_QKV, EPI_RESID and EPI_DOWN on the
+// balanced path: thread t holds elements (row (t + 256 e) / 32, column t % 32),
+// e < 2 MT, so a row is one half-wave and its sums and rotation partners are
+// cross-lane moves.  What the epilogue reads from memory depends on the pair
+// alone: a workgroup's first unit is read ahead (load, then angles once the
+// row positions have arrived) while its weights stream, instead of two to
+// four dependent round trips at the end.
+template <bool BF, int MT, int EPI> struct UnitEpi {
+  static constexpr int NE = 2 * MT;
+  float c0 = 0.f, c1 = 0.f;      // column: gain, or bias and the partner's bias
+  float x[NE];                   // residual
+  int pos[NE], slot[NE];         // cache row and slot
+  float cs[NE], sn[NE];          // rotation
+  int pair = -1;
+
+  __device__ __forceinline__ static int row_of(int e) { return (int)(threadIdx.x >> 5) + 8 * e; }
+  // QKV: head, rotation index, half and output column of this thread's column
+  struct Col {
+    int head, i, j, n;
+  };
+  __device__ __forceinline__ Col col(const GemmArgs& p) const {
+    const int c = threadIdx.x & 31, d = p.head_dim, ppd = d / kPairCols;
+    Col k;
+    k.head = pair / ppd;
+    k.j = c >> 4;
+    k.i = 16 * (pair - k.head * ppd) + (c & 15);
+    k.n = k.head * d + k.j * (d >> 1) + k.i;
+    return k;
+  }
+  __device__ __forceinline__ void load(const GemmArgs& p, int M, int pr) {
+    pair = pr;
+    if constexpr (EPI == EPI_QKV) {
+      const Col k = col(p);
+      if (p.bias) {
+        const int half = p.head_dim >> 1;
+        c0 = ldg(p.bias + k.n);
+        c1 = ldg(p.bias + (k.j ? k.n - half : k.n + half));
+      }
+#pragma unroll
+      for (int e = 0; e < NE; ++e) {
+        const RowDesc* r = p.rows + min(row_of(e), M - 1);
+        pos[e] = ldg(&r->pos);
+        slot[e] = ldg(&r->slot);
+      }
+    } else {
+      const int n = pair * kPairCols + (threadIdx.x & 31);
+      c0 = ldg(p.gain_next + n);
+#pragma unroll
+      for (int e = 0; e < NE; ++e) x[e] = ldg(p.x + (size_t)min(row_of(e), M - 1) * p.N + n);
+    }
+  }
+  __device__ __forceinline__ void angles(const GemmArgs& p) {
+    if constexpr (EPI == EPI_QKV) {
+      const Col k = col(p);
+#pragma unroll
+      for (int e = 0; e < NE; ++e) {
+        const float2 a = ldg(reinterpret_cast<const float2*>(p.rope_cs) + (size_t)pos[e] * (p.head_dim >> 1) + k.i);
+        cs[e] = a.x;
+        sn[e] = a.y;
+      }
+    }
+  }
+  // the finished sums f of the pair (row-scaled)
+  template <bool COH> __device__ __forceinline__ void finish(const GemmArgs& p, int M, const float (&f)[NE]) const {
+#pragma clang fp contract(off)
+    if constexpr (EPI == EPI_QKV) {
+      const int d = p.head_dim;
+      const Col k = col(p);
+      const int dd = k.n - k.head * d;
+#pragma unroll
+      for (int e = 0; e < NE; ++e) {
+        const int m = row_of(e);
+        float v = f[e] + c0;
+        const float partner = swizzle_xor16(f[e]) + c1;
+        if (m >= M) continue;
+        if (k.head < p.n_q + p.n_kv) {
+          v = rope(v, k.j == 0 ? -partner : partner, cs[e], sn[e]);
+          if (k.head < p.n_q) {
+            st<COH>(p.q_out + (size_t)m * p.n_q * d + k.n, v);
+            continue;
+          }
+          float* kb = p.k_cache + (size_t)slot[e] * p.slot_stride + (size_t)(k.head - p.n_q) * p.kv_cap * d;
+          if constexpr (BF) {
+            uint16_t* k16 = reinterpret_cast<uint16_t*>(kb) + (size_t)pos[e] * 2 * d + dd;
+            const BfPair h = split_val(v);
+            st<COH>(k16, h.hi);
+            st<COH>(k16 + d, h.lo);
+          } else {
+            st<COH>(kb + (size_t)pos[e] * d + dd, v);
+          }
+        } else {
+          float* vb = p.v_cache + (size_t)slot[e] * p.slot_stride + (size_t)(k.head - p.n_q - p.n_kv) * p.kv_cap * d;
+          if constexpr (BF) {
+            uint16_t* v16 = reinterpret_cast<uint16_t*>(vb);
+            const BfPair h = split_val(v);
+            st<COH>(v16 + v_elem(pos[e], 0, dd, d, true), h.hi);
+            st<COH>(v16 + v_elem(pos[e], 1, dd, d, true), h.lo);
+          } else {
+            st<COH>(vb + v_elem(pos[e], 0, dd, d, false), v);
+          }
+        }
+      }
+    } else {
+      const int n = pair * kPairCols + (threadIdx.x & 31);
+#pragma unroll
+      for (int e = 0; e < NE; ++e) {
+        const int m = row_of(e);
+        const float v = x[e] + f[e];
+        const float s = half_sumsq(v);
+        if (m >= M) continue;
+        st<COH>(p.x_out + (size_t)m * p.N + n, v);
+        store_act_mul<BF, COH>(p.out, p.out_plane, frag_index<BF>(m, n, p.N), v, c0);
+        if ((threadIdx.x & 31) == 0) st<COH>(p.sumsq_out + (size_t)m * (p.N / kPairCols) + pair, s);
+      }
+    }
+  }
+};
+
 // After the stream of the balanced path (s_scale already holds the row
 // scales): the epilogue of units [u0, u0 + nu) from their sums in F, or,
 // with k-splits, their partials and the fixup and epilogue of each pair
-// whose last split arrives in this workgroup.
+// whose last split arrives in this workgroup.  `first`: the first unit's
+// epilogue operands, read ahead.
+template <bool BF, int MT, int AM, int EPI, bool COH>
+__device__ __forceinline__ void range_finish_units(const GemmArgs& p, int M, float* F, int fs, int u0, int nu,
+                                                   const float* s_scale, int* s_flags, UnitEpi<BF, MT, EPI>& first) {
+#pragma clang fp contract(off)
+  using E = UnitEpi<BF, MT, EPI>;
+  const int tid = threadIdx.x, KS = p.KS;
+  auto epilogue = [&](int j, const float (&f)[E::NE]) {
+    if (j == 0) {
+      first.template finish<COH>(p, M, f);
+    } else {
+      E e;
+      e.load(p, M, (u0 + j) / KS);
+      e.angles(p);
+      e.template finish<COH>(p, M, f);
+    }
+  };
+  if (KS == 1) {
+    for (int j = 0; j < nu; ++j) {
+      float f[E::NE];
+#pragma unroll
+      for (int e = 0; e < E::NE; ++e) {
+        const int m = min(E::row_of(e), M - 1);
+        const float v = F[m * fs + j * kPairCols + (tid & 31)];
+        f[e] = AM == A_NORM ? v * s_scale[m] : v;
+      }
+      epilogue(j, f);
+    }
+    return;
+  }
+  const int C = nu * kPairCols;
+  for (int e = tid; e < M * C; e += kWaves * 64) {
+    const int m = e / C, c = e - m * C;
+    const int u = u0 + c / kPairCols, pair = u / KS;
+    store_partial(&p.part[((size_t)(u - pair * KS) * M + m) * p.N + pair * kPairCols + (c & (kPairCols - 1))],
+                  F[m * fs + c]);
+  }
+  wait_vmem();
+  __syncthreads();  // every wave's partial stores are performed
+  if (tid < nu) {
+    const int pair = (u0 + tid) / KS;
+    const bool last = counter_add(&p.counters[pair], 1) == KS - 1;
+    if (last) st<true>(&p.counters[pair], 0);  // ready for the next launch
+    s_flags[tid] = last;
+  }
+  __syncthreads();
+  for (int j = 0; j < nu; ++j) {
+    if (!s_flags[j]) continue;
+    const int n = (u0 + j) / KS * kPairCols + (tid & 31);
+    float v[E::NE][kMaxSplits];
+#pragma unroll
+    for (int e = 0; e < E::NE; ++e)
+#pragma unroll
+      for (int sp = 0; sp < kMaxSplits; ++sp)
+        if (sp < KS) v[e][sp] = load_partial(&p.part[((size_t)sp * M + min(E::row_of(e), M - 1)) * p.N + n]);
+    float f[E::NE];
+#pragma unroll
+    for (int e = 0; e < E::NE; ++e) {
+      f[e] = v[e][0];
+#pragma unroll
+      for (int sp = 1; sp < kMaxSplits; ++sp)
+        if (sp < KS) f[e] += v[e][sp];
+      if constexpr (AM == A_NORM) f[e] *= s_scale[min(E::row_of(e), M - 1)];
+    }
+    epilogue(j, f);
+  }
+}
+
+// The same for the epilogues without operands in memory (SwiGLU, arg-max),
+// over all the workgroup's pairs at once.
 template <bool BF, int AM, int EPI, bool COH>
 __device__ __forceinline__ void range_finish(const GemmArgs& p, int M, float* F, int fs, int u0, int nu, const float* s_scale,
                              int* s_flags) {
@@ -765,9 +953,13 @@ __device__ __forceinline__ void gemm_range_direct(const GemmArgs& p, int M, unsi
       advance(ca);
     }
   }
+  constexpr bool UNITS = EPI == EPI_QKV || EPI == EPI_RESID || EPI == EPI_DOWN;
+  UnitEpi<BF, MT, UNITS ? EPI : EPI_RESID> first;
+  if constexpr (UNITS) first.load(p, M, u0 / KS);
   constexpr int RPW = MT * 16 / kWaves;
   float rs[RPW];
   row_scale_loads<AM, RPW>(p, M, rs);                 // read while the first weights arrive
+  if constexpr (UNITS) first.angles(p);
   int cj = 0;                                         // unit being summed
   for (int i = 0; i < S; i += P) {
 #pragma unroll
@@ -794,7 +986,8 @@ __device__ __forceinline__ void gemm_range_direct(const GemmArgs& p, int M, unsi
   }
   row_scale_finish<AM, RPW>(p, M, rs, s_scale);
   lds_sync();                                         // the last unit's sums are in F
-  range_finish<BF, AM, EPI, COH>(p, M, F, fs, u0, nu, s_scale, s_flags);
+  if constexpr (UNITS) range_finish_units<BF, MT, AM, EPI, COH>(p, M, F, fs, u0, nu, s_scale, s_flags, first);
+  else range_finish<BF, AM, EPI, COH>(p, M, F, fs, u0, nu, s_scale, s_flags);
 }
 
 // The balanced path for KS = 1 and one row tile when every wave's slice
