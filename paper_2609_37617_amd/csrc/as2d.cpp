@@ -372,7 +372,10 @@ int launch_pass(as2d_ctx* c, const PassBufs& B, int M, int n_att, int n_fin, int
   const int mr = g.max_requests;
   {
     Timed t(c, K_EMBED);
-    HIP_TRY(c, launch_embed(bf, B.d_rows, M, c->embed, c->audio, g.hidden, c->layers[0].g_attn, B.x,
+    // a prefill's descriptors have been copied; the others are read in place
+    PassDesc put;
+    if (!prefill) put = PassDesc{B.d_rows, c->h_reqs, B.d_reqs, n_att, mr, n_fin};
+    HIP_TRY(c, launch_embed(bf, prefill ? B.d_rows : c->h_rows, put, M, c->embed, c->audio, g.hidden, c->layers[0].g_attn, B.x,
                             B.sumsq, B.xg, B.xg_plane, s));
   }
   const int d = g.head_dim;
@@ -478,8 +481,8 @@ int launch_pass(as2d_ctx* c, const PassBufs& B, int M, int n_att, int n_fin, int
     {
       Timed t(c, K_FINISH);
       HIP_TRY(c, launch_finish(B.d_rows, B.d_reqs + mr, n_fin, fin_rows, B.amax_val, B.amax_val2, B.amax_idx,
-                               g.vocab / kPairCols, B.row_tok, B.row_bad, B.row_margin, B.fin_counters,
-                               B.d_out, s));
+                               g.vocab / kPairCols, B.row_tok, B.row_bad, B.fin_counters,
+                               HostOut{c->h_tok, c->h_margin, c->h_out}, s));
     }
   }
   return AS2D_OK;
@@ -689,8 +692,6 @@ int run_forward(as2d_ctx* c, int M, int n_att, int n_fin, bool with_head, bool v
   const int mr = g.max_requests;
   int fin_rows = 0;
   for (int r = 0; r < n_fin; ++r) fin_rows += c->h_reqs[mr + r].W;
-  HIP_TRY(c, hipMemcpyAsync(c->b.d_rows, c->h_rows, sizeof(RowDesc) * M, hipMemcpyHostToDevice, s));
-  HIP_TRY(c, hipMemcpyAsync(c->b.d_reqs, c->h_reqs, sizeof(ReqDesc) * 2 * mr, hipMemcpyHostToDevice, s));
   int max_blocks = 1;
   for (int r = 0; r < n_att; ++r) {
     const int nk = c->h_reqs[r].L0 + c->h_reqs[r].W;
@@ -701,6 +702,10 @@ int run_forward(as2d_ctx* c, int M, int n_att, int n_fin, bool with_head, bool v
   const bool persistent = verify_pass && c->exec_mode == AS2D_EXEC_PERSISTENT && c->pers_ok && c->pers_fit && M <= kStepRows;
   const bool graph = verify_pass && c->exec_mode != AS2D_EXEC_EAGER && !c->timing;
   if (persistent && !step_layers_for(c, M)) return fail(c, AS2D_ENOMEM, "persistent step arguments");
+  if (persistent || !verify_call) {   // the other passes read and write the host's arrays themselves
+    HIP_TRY(c, hipMemcpyAsync(c->b.d_rows, c->h_rows, sizeof(RowDesc) * M, hipMemcpyHostToDevice, s));
+    HIP_TRY(c, hipMemcpyAsync(c->b.d_reqs, c->h_reqs, sizeof(ReqDesc) * 2 * mr, hipMemcpyHostToDevice, s));
+  }
   if (graph) {
     hipGraphExec_t ex = nullptr;
     int rc = graph_for(c, M, n_att, n_fin, fin_rows, persistent, &ex);
@@ -712,11 +717,10 @@ int run_forward(as2d_ctx* c, int M, int n_att, int n_fin, bool with_head, bool v
     if (rc) return rc;
   }
   if (persistent) HIP_TRY(c, hipMemcpyAsync(&c->h_err, c->perr, sizeof(int), hipMemcpyDeviceToHost, s));
-  if (with_head) {
+  if (persistent) {
     HIP_TRY(c, hipMemcpyAsync(c->h_out, c->b.d_out, sizeof(StepOut) * n_fin, hipMemcpyDeviceToHost, s));
-    const int n_rows = verify_call ? M : (M - 1) % 16 + 1;
-    HIP_TRY(c, hipMemcpyAsync(c->h_tok, c->b.row_tok, sizeof(int) * n_rows, hipMemcpyDeviceToHost, s));
-    HIP_TRY(c, hipMemcpyAsync(c->h_margin, c->b.row_margin, sizeof(float) * n_rows, hipMemcpyDeviceToHost, s));
+    HIP_TRY(c, hipMemcpyAsync(c->h_tok, c->b.row_tok, sizeof(int) * M, hipMemcpyDeviceToHost, s));
+    HIP_TRY(c, hipMemcpyAsync(c->h_margin, c->b.row_margin, sizeof(float) * M, hipMemcpyDeviceToHost, s));
   }
   HIP_TRY(c, hipStreamSynchronize(s));
   timing_collect(c);
@@ -915,7 +919,6 @@ size_t static_layout(const as2d_ctx* c, int n_blocks, char* base, PassBufs* S) {
     if (p->KS > 1) part = std::max(part, (size_t)p->KS * R * p->N);
   S->d_rows = (RowDesc*)take(sizeof(RowDesc) * R);
   S->d_reqs = (ReqDesc*)take(sizeof(ReqDesc) * 2 * g.max_requests);
-  S->d_out = (StepOut*)take(sizeof(StepOut) * g.max_requests);
   S->x = (float*)take(R * H * 4);
   S->q = (float*)take(R * QD * 4);
   S->xg = take(R * H * 4);
@@ -933,17 +936,17 @@ size_t static_layout(const as2d_ctx* c, int n_blocks, char* base, PassBufs* S) {
   S->amax_idx = (int*)take((V / kPairCols) * R * 4);
   S->row_tok = (int*)take(R * 4);
   S->row_bad = (int*)take(R * 4);
-  S->row_margin = (float*)take(R * 4);
-  S->fin_counters = (int*)take((size_t)g.max_requests * 4);
   S->part = (float*)take(part * 4);
   S->part_elems = part;
   S->n_counters = split_counter_count(c, kStaticRows);
+  // the counters, in one run (cleared together)
   S->counters = (int*)take((size_t)S->n_counters * 4);
+  S->fin_counters = (int*)take((size_t)g.max_requests * 4);
+  S->attn_cnt = (int*)take((size_t)g.max_requests * g.n_q_heads * 2 * 4);
   S->part_spans = (int)((n_blocks + kAttnSpan - 1) / kAttnSpan);
   const size_t spans = (n_blocks + kAttnSpan - 1) / kAttnSpan;
   S->pacc = (float*)take(spans * R * QD * 4);
   S->pml = (float*)take(spans * R * g.n_q_heads * 2 * 4);
-  S->attn_cnt = (int*)take((size_t)g.max_requests * g.n_q_heads * 2 * 4);
   return off;
 }
 
@@ -1344,20 +1347,13 @@ int as2d_verify_static(as2d_ctx* c, int32_t req, const int32_t* cands, int32_t k
     return fail(c, AS2D_ECAPACITY, "verify_static: the pass needs %zu bytes of static scratch, %zu available (%d keys)",
                 need, cap, c->h_reqs[0].L0 + M);
   hipStream_t s = c->stream;
-  HIP_TRY(c, hipMemcpyAsync(S.d_rows, c->h_rows, sizeof(RowDesc) * M, hipMemcpyHostToDevice, s));
-  HIP_TRY(c, hipMemcpyAsync(S.d_reqs, c->h_reqs, sizeof(ReqDesc) * 2 * mr, hipMemcpyHostToDevice, s));
   // the array keeps the last call's contents: counters must start at zero
-  HIP_TRY(c, launch_fill_zero(S.counters, S.n_counters, s));
-  HIP_TRY(c, launch_fill_zero(S.fin_counters, mr, s));
-  HIP_TRY(c, launch_fill_zero(S.attn_cnt, mr * g.n_q_heads * 2, s));
+  HIP_TRY(c, launch_fill_zero(S.counters, (int)(S.attn_cnt - S.counters) + mr * g.n_q_heads * 2, s));
   const int timing = c->timing;   // no event bracketing here (events are created on first use)
   c->timing = 0;
   rc = launch_pass(c, S, M, 1, 1, M, true, n_blocks, false);
   c->timing = timing;
   if (rc) return rc;
-  HIP_TRY(c, hipMemcpyAsync(c->h_out, S.d_out, sizeof(StepOut), hipMemcpyDeviceToHost, s));
-  HIP_TRY(c, hipMemcpyAsync(c->h_tok, S.row_tok, sizeof(int) * M, hipMemcpyDeviceToHost, s));
-  HIP_TRY(c, hipMemcpyAsync(c->h_margin, S.row_margin, sizeof(float) * M, hipMemcpyDeviceToHost, s));
   HIP_TRY(c, hipStreamSynchronize(s));
   return commit_verify(c, 1, &req, &k, out);
 }

@@ -65,6 +65,22 @@ struct StepOut {
   int32_t accepted, correction, nan_flag, pad;
 };
 
+// Where the first kernel of a pass puts descriptors it reads from pinned host
+// memory (rows null: they are on the device already): rows, and requests
+// [0, n_att) and [fin0, fin0 + n_fin) of reqs_in.
+struct PassDesc {
+  RowDesc* rows = nullptr;
+  const ReqDesc* reqs_in = nullptr;
+  ReqDesc* reqs = nullptr;
+  int n_att = 0, fin0 = 0, n_fin = 0;
+};
+// Results of a pass in pinned host memory: per row, per request.
+struct HostOut {
+  int* tok;
+  float* margin;
+  StepOut* req;
+};
+
 enum AMode { A_PLAIN = 0, A_NORM = 1 };
 // EPI_DOWN is EPI_RESID under its own id: the O and down projections then
 // run as distinct kernel instantiations, so profiles attribute them apart.
@@ -217,7 +233,7 @@ hipError_t prepare_step_kernels();
 // map: PackMap; arg: F for PACK_GATE_UP, the head dimension for PACK_ROPE_PAIRS.
 hipError_t launch_pack(bool bf16, const void* src, uint4* dst, int N, int K, int map, int arg,
                        hipStream_t s);
-hipError_t launch_embed(bool bf16, const RowDesc* rows, int M, const void* embed, const void* audio,
+hipError_t launch_embed(bool bf16, const RowDesc* rows, const PassDesc& put, int M, const void* embed, const void* audio,
                         int H, const float* gain, float* x, float* sumsq, void* xg, long long xg_plane,
                         hipStream_t s);
 hipError_t launch_gemm(bool bf16, int amode, int epi, const GemmArgs& a, hipStream_t s);
@@ -244,11 +260,11 @@ hipError_t launch_attention(bool bf16, const AttnArgs& a, int n_reqs, int max_bl
 hipError_t launch_attn_prefill(const AttnArgs& a, hipStream_t s);
 hipError_t prepare_attn_prefill();
 // n_rows = sum of the requests' W; counters: one per request, zero between launches.
-// Writes each verified row's greedy token, non-finite flag and top-2 margin.
+// Writes each verified row's greedy token, non-finite flag and top-2 margin,
+// and each request's outcome.
 hipError_t launch_finish(const RowDesc* rows, const ReqDesc* reqs, int n_reqs, int n_rows,
                          const float* amax_val, const float* amax_val2, const int* amax_idx, int n_pairs,
-                         int* row_tok, int* row_bad, float* row_margin, int* counters, StepOut* out,
-                         hipStream_t s);
+                         int* row_tok, int* row_bad, int* counters, const HostOut& out, hipStream_t s);
 
 // Zeroes n ints (a kernel, not a memset, so that it may be captured).
 hipError_t launch_fill_zero(int* p, int n, hipStream_t s);

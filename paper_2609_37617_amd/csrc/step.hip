@@ -112,8 +112,8 @@ __global__ __launch_bounds__(256, 1) void step_kernel(const StepArgs a) {
   // embedding rows
   stamp(a, 0, 0);
   for (int m = blockIdx.x; m < M; m += G) {
-    embed_row<BF, true>(a.rows, m, (const typename ET<BF>::T*)a.embed, (const typename ET<BF>::T*)a.audio,
-                        a.hidden, a.gain0, a.x0, a.sumsq0, a.xg0, a.xg0_plane, reinterpret_cast<float*>(smem));
+    embed_row<BF, true>(load_invariant(a.rows + m), m, (const typename ET<BF>::T*)a.embed, (const typename ET<BF>::T*)a.audio,
+                        a.hidden, a.gain0, a.x0, a.sumsq0, a.xg0, a.xg0_plane);
     signal_done(&a.phase_cnt[0]);
   }
 

@@ -10,21 +10,21 @@
 namespace as2d {
 
 // ---------------------------------------------------------------------------
-// Embedding gather of row m: residual x (float32) from a token embedding or
-// an audio staging row, the planes of x * g for the first RMSNorm (gain g),
-// and the row's sum-of-squares partials per 32-column pair.  256 threads;
-// srow: LDS scratch of H floats.
+// Embedding gather of row m (descriptor rd): residual x (float32) from a
+// token embedding or an audio staging row, the planes of x * g for the first
+// RMSNorm (gain g), and the row's sum-of-squares partials per 32-column pair.
+// 256 threads, eight consecutive columns each; four neighbours hold a pair
+// (the sums of half_sumsq).
 
 template <bool BF, bool COH>
-__device__ __forceinline__ void embed_row(const RowDesc* __restrict__ rows, int m, const typename ET<BF>::T* __restrict__ embed,
+__device__ __forceinline__ void embed_row(const RowDesc& rd, int m, const typename ET<BF>::T* __restrict__ embed,
                           const typename ET<BF>::T* __restrict__ audio, int H, const float* __restrict__ gain,
                           float* __restrict__ x, float* __restrict__ sumsq, void* __restrict__ xg,
-                          long long xg_plane, float* srow) {
+                          long long xg_plane) {
   using T = typename ET<BF>::T;
-  constexpr int kPer = 8, kPasses = 4;   // H <= 256 * 8 * 4
-  const RowDesc rd = load_invariant(rows + m);
+  constexpr int kPer = 8, kPasses = 4;   // H <= 256 * 8 * 4, a multiple of 128
   const T* src = rd.token >= 0 ? embed + (size_t)rd.token * H : audio + (size_t)rd.src * H;
-  float v[kPasses][kPer];
+  float v[kPasses][kPer], g[kPasses][kPer];
 #pragma unroll
   for (int ps = 0; ps < kPasses; ++ps) {
     const int c0 = (ps * 256 + threadIdx.x) * kPer;
@@ -43,29 +43,48 @@ __device__ __forceinline__ void embed_row(const RowDesc* __restrict__ rows, int 
         v[ps][0] = a.x; v[ps][1] = a.y; v[ps][2] = a.z; v[ps][3] = a.w;
         v[ps][4] = b.x; v[ps][5] = b.y; v[ps][6] = b.z; v[ps][7] = b.w;
       }
+      const float4 a = *reinterpret_cast<const float4*>(gain + c0), b = *reinterpret_cast<const float4*>(gain + c0 + 4);
+      g[ps][0] = a.x; g[ps][1] = a.y; g[ps][2] = a.z; g[ps][3] = a.w;
+      g[ps][4] = b.x; g[ps][5] = b.y; g[ps][6] = b.z; g[ps][7] = b.w;
     }
   }
+  // N words, 16 bytes at a time (agent-scope stores are 4 bytes)
+  auto put = [](void* p, const uint32_t* w, int n) {
+    if constexpr (COH) {
+      for (int t = 0; t < n; ++t) st<true>(static_cast<uint32_t*>(p) + t, w[t]);
+    } else {
+      for (int t = 0; t < n; t += 4) *gmem(static_cast<u32x4*>(p) + t / 4) = u32x4{w[t], w[t + 1], w[t + 2], w[t + 3]};
+    }
+  };
 #pragma unroll
   for (int ps = 0; ps < kPasses; ++ps) {
     const int c0 = (ps * 256 + threadIdx.x) * kPer;
     if (c0 < H) {
+      uint32_t w[kPer];
 #pragma unroll
-      for (int t = 0; t < kPer; ++t) {
-        st<COH>(x + (size_t)m * H + c0 + t, v[ps][t]);
-        store_act_mul<BF, COH>(xg, xg_plane, frag_index<BF>(m, c0 + t, H), v[ps][t], gain[c0 + t]);
-        srow[c0 + t] = v[ps][t];
+      for (int t = 0; t < kPer; ++t) w[t] = __float_as_uint(v[ps][t]);
+      put(x + (size_t)m * H + c0, w, kPer);
+      const size_t o = frag_index<BF>(m, c0, H);   // eight columns lie in one k-step block
+      if constexpr (BF) {
+        uint32_t h[4], l[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const BfPair a = split_mul(v[ps][2 * t], g[ps][2 * t]), b = split_mul(v[ps][2 * t + 1], g[ps][2 * t + 1]);
+          h[t] = a.hi | ((uint32_t)b.hi << 16);
+          l[t] = a.lo | ((uint32_t)b.lo << 16);
+        }
+        put(static_cast<uint16_t*>(xg) + o, h, 4);
+        put(static_cast<uint16_t*>(xg) + o + xg_plane, l, 4);
+      } else {
+#pragma unroll
+        for (int t = 0; t < kPer; ++t) w[t] = __float_as_uint(v[ps][t] * g[ps][t]);
+        put(static_cast<float*>(xg) + o, w, kPer);
       }
+      float s = sumsq8(v[ps]);
+      s = s + dpp_get<kDppXor1>(s);
+      s = s + dpp_get<kDppXor2>(s);
+      if ((threadIdx.x & 3) == 0) st<COH>(sumsq + (size_t)m * (H / kPairCols) + c0 / kPairCols, s);
     }
-  }
-  lds_sync();
-  // one pair per half-wave
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int n_pairs = H / kPairCols;
-  for (int u0 = wave * 2; u0 < n_pairs; u0 += 8) {
-    const int g = u0 + (lane >> 5);
-    const float e = g < n_pairs ? srow[g * kPairCols + (lane & 31)] : 0.0f;
-    const float s = half_sumsq(e);
-    if ((lane & 31) == 0 && g < n_pairs) st<COH>(sumsq + (size_t)m * n_pairs + g, s);
   }
 }
 
