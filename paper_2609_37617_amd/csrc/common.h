@@ -360,6 +360,45 @@ __device__ __forceinline__ void half_argmax(float& v, int& i) {
   }
 }
 
+// Sums and lookups over a pass's request descriptors, one request per lane (a
+// loop over them costs a memory round trip per request).  `f(rq)` is a
+// request's count; every lane of the wave takes part and gets the result.
+__device__ __forceinline__ ReqDesc lane_request(const ReqDesc* reqs, int r) {
+  const uint4 v = ldg(reinterpret_cast<const uint4*>(reqs + r));
+  return ReqDesc{(int32_t)v.x, (int32_t)v.y, (int32_t)v.z, (int32_t)v.w};
+}
+template <class F> __device__ __forceinline__ int sum_requests(const ReqDesc* reqs, int n, F&& f) {
+  const int lane = threadIdx.x & 63;
+  int total = 0;
+  for (int i = 0; i < n; i += 64) {
+    int c = i + lane < n ? f(lane_request(reqs, i + lane)) : 0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
+    total += __builtin_amdgcn_readfirstlane(c);
+  }
+  return total;
+}
+// The request that holds unit u of the requests' units in order; u becomes its
+// place among the request's own.  -1 past the last.
+template <class F> __device__ __forceinline__ int find_request(const ReqDesc* reqs, int n, int& u, F&& f) {
+  const int lane = threadIdx.x & 63;
+  for (int i = 0; i < n; i += 64) {
+    int s = i + lane < n ? f(lane_request(reqs, i + lane)) : 0;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int t = __shfl_up(s, o);
+      if (lane >= o) s += t;
+    }
+    const int k = __popcll(__ballot(s <= u));   // requests that end at or before u
+    if (k < 64) {
+      if (k) u -= __builtin_amdgcn_readlane(s, k - 1);
+      return i + k < n ? i + k : -1;
+    }
+    u -= __builtin_amdgcn_readlane(s, 63);
+  }
+  return -1;
+}
+
 // Workgroups are dealt to the 8 XCDs round-robin by linear index.  The
 // index v of the work a block takes: XCD j's blocks take one contiguous
 // range of v (the first n % 8 XCDs one more each), in dispatch order.

@@ -322,31 +322,30 @@ __device__ __forceinline__ void attn_group_items(const AttnArgs& p, int n_reqs, 
   // an item covers a run of up to R consecutive spans: the least R whose
   // items fit the grid (one span each while they do; long caches take
   // several per workgroup)
-  int ns_max = 1;
-  auto n_items = [&](int R) {
-    int n = 0;
-    for (int r = 0; r < n_reqs; ++r) {
-      const ReqDesc rq = load_invariant(p.reqs + r);
-      const int ns = (rq.L0 + rq.W - 1) / kAttnSpanKeys + 1;
-      ns_max = max(ns_max, ns);
-      n += p.n_kv * blocks(rq) * ((ns + R - 1) / R);
-    }
-    return n;
+  const auto items = [&](const ReqDesc& rq, int R) {
+    const int ns = (rq.L0 + rq.W - 1) / kAttnSpanKeys + 1;
+    return p.n_kv * blocks(rq) * ((ns + R - 1) / R);
+  };
+  const auto n_items = [&](int R) {
+    if (n_reqs == 1) return items(load_invariant(p.reqs), R);
+    return sum_requests(p.reqs, n_reqs, [&](const ReqDesc& rq) { return items(rq, R); });
   };
   int R = 1, total = n_items(1);
-  while (total > G && R < ns_max) total = n_items(++R);
+  if (total > G) {
+    // no run length gives fewer items than one run per block, nor, below
+    // total / G, few enough
+    const int least = n_reqs == 1 ? p.n_kv * blocks(load_invariant(p.reqs))
+                                  : sum_requests(p.reqs, n_reqs, [&](const ReqDesc& rq) { return p.n_kv * blocks(rq); });
+    R = (total + G - 1) / G;
+    total = n_items(R);
+    while (total > G && total > least) total = n_items(++R);
+  }
   for (int t = xcd_contiguous(blockIdx.x, G); t < total; t += G) {
     // item t: request r, then run j, KV head g, row block b
-    int r = 0, u = t, ns = 0, nb = 0;
-    ReqDesc rq;
-    for (;; ++r) {
-      rq = load_invariant(p.reqs + r);
-      ns = (rq.L0 + rq.W - 1) / kAttnSpanKeys + 1;
-      nb = blocks(rq);
-      const int n = p.n_kv * nb * ((ns + R - 1) / R);
-      if (u < n || r == n_reqs - 1) break;
-      u -= n;
-    }
+    int u = t;
+    const int r = n_reqs == 1 ? 0 : find_request(p.reqs, n_reqs, u, [&](const ReqDesc& q) { return items(q, R); });
+    const ReqDesc rq = load_invariant(p.reqs + r);
+    const int ns = (rq.L0 + rq.W - 1) / kAttnSpanKeys + 1, nb = blocks(rq);
     const int j = u / (p.n_kv * nb);
     const int v = u - j * p.n_kv * nb;
     const int g = v / nb, b = v - g * nb;
@@ -427,13 +426,15 @@ __global__ __launch_bounds__(256) void attn_group_kernel(const AttnArgs p, int n
   int rt = p.attn_rt;
   if (rt != 1 && rt != 2) {
     const int hpg = p.n_q / p.n_kv;
-    int n1 = 0, n2 = 0;   // items with one-tile and two-tile blocks, one span each
-    for (int r = 0; r < n_reqs; ++r) {
-      const ReqDesc rq = load_invariant(p.reqs + r);
-      const int ns = (rq.L0 + rq.W - 1) / kAttnSpanKeys + 1;
-      n1 += p.n_kv * ((hpg * rq.W + 15) / 16) * ns;
-      n2 += p.n_kv * ((hpg * rq.W + 31) / 32) * ns;
-    }
+    // items with one-tile and two-tile blocks, one span each
+    const auto items = [&](const ReqDesc& rq, int rows) {
+      return p.n_kv * ((hpg * rq.W + rows - 1) / rows) * ((rq.L0 + rq.W - 1) / kAttnSpanKeys + 1);
+    };
+    const auto n_items = [&](int rows) {
+      if (n_reqs == 1) return items(load_invariant(p.reqs), rows);
+      return sum_requests(p.reqs, n_reqs, [&](const ReqDesc& rq) { return items(rq, rows); });
+    };
+    const int n1 = n_items(16), n2 = n_items(32);
     rt = n1 <= (int)gridDim.x || 2 * n1 < 3 * n2 ? 1 : 2;
   }
   if (rt == 1) attn_group_items<BF, D, 1>(p, n_reqs, smem);
@@ -451,14 +452,11 @@ __global__ __launch_bounds__(256, 2) void attn_group2_kernel(const AttnArgs p, i
 // One wave per (request row, query head), heads of a row adjacent.
 template <bool BF, int D>
 __global__ __launch_bounds__(64) void attn_merge_kernel(const AttnArgs p, int n_reqs) {
-  int u = blockIdx.x;
-  ReqDesc rq;
-  for (int r = 0;; ++r) {
-    if (r == n_reqs) return;
-    rq = load_invariant(p.reqs + r);
-    if (u < rq.W * p.n_q) break;
-    u -= rq.W * p.n_q;
-  }
+  int u = blockIdx.x, r = 0;
+  if (n_reqs > 1) r = find_request(p.reqs, n_reqs, u, [&](const ReqDesc& q) { return q.W * p.n_q; });
+  if (r < 0) return;
+  const ReqDesc rq = load_invariant(p.reqs + r);
+  if (u >= rq.W * p.n_q) return;
   const int i = u / p.n_q;
   attn_merge_wave<BF, D>(p, rq, i, u - i * p.n_q);
 }
@@ -664,8 +662,9 @@ __global__ __launch_bounds__(256) void finish_kernel(const RowDesc* __restrict__
   __shared__ int s4i[4];
   __shared__ int s_tok, s_bad;
   __shared__ float s_margin;
-  int r = 0, i = blockIdx.x;
-  while (r < n_reqs - 1 && i >= reqs[r].W) i -= reqs[r++].W;
+  int r = 0, i = blockIdx.x;   // the grid is the sum of the requests' rows
+  if (n_reqs > 1) r = find_request(reqs, n_reqs, i, [](const ReqDesc& q) { return q.W; });
+  if (r < 0) return;
   const ReqDesc rq = reqs[r];
   const int row = rq.row_start + i;
   argmax_row<false>(amax_val, amax_val2, amax_idx, n_pairs, row, &s_tok, &s_bad, &s_margin, s4f, s4s, s4i);

@@ -885,7 +885,8 @@ __device__ __forceinline__ void gemm_range_direct(const GemmArgs& p, int M, unsi
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int KS = p.KS, KT = p.KT, G = p.G;
   const int U = (p.N / kPairCols) * KS;
-  const int u0 = (int)((long long)blockIdx.x * U / G), u1 = (int)((long long)(blockIdx.x + 1) * U / G);
+  // U <= kMaxUnits G, so the products fit 32 bits
+  const int u0 = blockIdx.x * (uint32_t)U / (uint32_t)G, u1 = (blockIdx.x + 1) * (uint32_t)U / (uint32_t)G;
   const int nu = u1 - u0;
   const int fs = ((U + G - 1) / G) * kPairCols + 1;
   float* R = reinterpret_cast<float*>(smem);         // [unit & 1][wave][mt][j][i][lane]
@@ -904,11 +905,16 @@ __device__ __forceinline__ void gemm_range_direct(const GemmArgs& p, int M, unsi
     c.kt = slice_start(kt0, n_all, wave, kWaves);
     c.end = slice_start(kt0, n_all, wave + 1, kWaves);
   };
-  int S = 0;                                          // k-steps of this wave
-  for (int j = 0; j < nu; ++j) {
-    Cur c;
-    set_unit(c, j);
-    S += c.end - c.kt;
+  // k-steps of this wave (without splits every unit has the same)
+  int S = 0;
+  if (KS == 1) {
+    S = nu * (slice_start(0, KT, wave + 1, kWaves) - slice_start(0, KT, wave, kWaves));
+  } else {
+    for (int j = 0; j < nu; ++j) {
+      Cur c;
+      set_unit(c, j);
+      S += c.end - c.kt;
+    }
   }
 
   const uint4* ap[MT];
@@ -1022,7 +1028,8 @@ __device__ __forceinline__ void gemm_range_direct_ra(const GemmArgs& p, int M, u
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int KT = p.KT, G = p.G;
   const int U = p.N / kPairCols;
-  const int u0 = (int)((long long)blockIdx.x * U / G), u1 = (int)((long long)(blockIdx.x + 1) * U / G);
+  // U <= kMaxUnits G, so the products fit 32 bits
+  const int u0 = blockIdx.x * (uint32_t)U / (uint32_t)G, u1 = (blockIdx.x + 1) * (uint32_t)U / (uint32_t)G;
   const int nu = u1 - u0;
   const int fs = ((U + G - 1) / G) * kPairCols + 1;
   float* R = reinterpret_cast<float*>(smem);
