@@ -29,6 +29,7 @@
 namespace as2d {
 
 constexpr int kPrefillWaves = 8;
+constexpr int kSpanWaves = 4;   // of the verification kernel below: two workgroups per compute unit
 
 // LDS: three buffers of a chunk's keys [32][4 D bytes] (a chunk's first keys
 // are read at the end of the chunk before) and two of its values [32 D 4
@@ -39,28 +40,32 @@ constexpr int kPrefillWaves = 8;
 template <int D> __host__ __device__ constexpr int attn_wide_units() { return 8 * D; }   // 16-byte units, keys or values
 template <int D> __host__ __device__ constexpr int attn_wide_lds_bytes() { return (3 + 2) * attn_wide_units<D>() * 16; }
 
-template <int D>
-__global__ __launch_bounds__(64 * kPrefillWaves, 2) void attn_prefill_wide_kernel(const AttnArgs p) {
+// attn_merge_coef for states that may be empty (M = -inf, L = 0, A = 0: the
+// identity): 2^(-inf - 0) = 0.
+__device__ __forceinline__ MergeCoef attn_coef0(float& M, float& L, float m, float l) {
 #pragma clang fp contract(off)
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  constexpr int KS = D / 32, DT = D / 16, U = attn_wide_units<D>(), NV = U / (64 * kPrefillWaves);
+  const float Mn = fmaxf(M, m), ref = Mn == -INFINITY ? 0.0f : Mn;
+  const MergeCoef k{exp2_hw(M - ref), exp2_hw(m - ref)};
+  L = __builtin_fmaf(L, k.a, l * k.c);
+  M = Mn;
+  return k;
+}
+
+// Chunks [c_first, c_end) (c_first the first of a span) of KV head g for the
+// NW waves' row tiles.  This lane's row sits at position pos and its queries
+// come from load_q once the first keys are requested; p0: a position no row
+// of the tile is before; last: the last key any of the workgroup's rows sees.
+// on_span(span, M, S, A) gets each span's state: A[t][i] is dimension
+// 16 t + 4 (lane / 16) + i.  Ends with the workgroup's barrier.
+template <int D, int NW, class LoadQ, class OnSpan>
+__device__ __forceinline__ void attn_walk(const AttnArgs& p, const ReqDesc& rq, int g, int p0, int pos, int last,
+                                          int c_first, int c_end, unsigned char* smem, LoadQ&& load_q, OnSpan&& on_span) {
+#pragma clang fp contract(off)
+  constexpr int KS = D / 32, DT = D / 16, U = attn_wide_units<D>(), NV = U / (64 * NW);
   constexpr int KU = D / 4;   // units of a key: hi, lo
   static_assert(NV >= 1, "whole units per thread");
-  const ReqDesc rq = load_invariant(p.reqs);
   const int tid = threadIdx.x, lane = tid & 63, lg = lane >> 4, lr = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int hpg = p.n_q / p.n_kv;
-  const int tiles = (rq.W + 15) / 16 * hpg, nw = (tiles + kPrefillWaves - 1) / kPrefillWaves;
-  const int g = blockIdx.x % p.n_kv, w = nw - 1 - blockIdx.x / p.n_kv;
-  const int T = min(w * kPrefillWaves + wave, tiles - 1);
-  const bool mine = w * kPrefillWaves + wave < tiles;
-  const int rt = T / hpg, h = g * hpg + (T - rt * hpg);
-  const int p0 = rq.L0 + rt * 16;                                 // position of the tile's first row
-  const int last = rq.L0 + min(rt * 16 + 15, rq.W - 1);           // ... and of its last one
-  const int pos = min(p0 + lr, last);                             // this lane's row (past the last: the last again)
-  const int last_all = rq.L0 + min(min((w + 1) * kPrefillWaves - 1, tiles - 1) / hpg * 16 + 15, rq.W - 1);
-  const int n_chunks = last_all / kAttnChunk + 1;
-
   const size_t head = (size_t)rq.slot * p.slot_stride + (size_t)g * p.kv_cap * D;   // float32 units
   const uint4* kb = reinterpret_cast<const uint4*>(p.k_cache + head);
   const uint4* vb = reinterpret_cast<const uint4*>(p.v_cache + head);
@@ -68,19 +73,19 @@ __global__ __launch_bounds__(64 * kPrefillWaves, 2) void attn_prefill_wide_kerne
 
   // this thread's units of a chunk: NV of its keys, NV of its values
   uint4 kr[NV], vr[NV];
-  auto request_k = [&](int c) {
+  auto request_k = [&](int c, uint4(&kr)[NV]) {
 #pragma unroll
-    for (int i = 0; i < NV; ++i) kr[i] = ldg(kb + (size_t)c * U + tid + i * 64 * kPrefillWaves);
+    for (int i = 0; i < NV; ++i) kr[i] = ldg(kb + (size_t)c * U + tid + i * 64 * NW);
   };
   auto request_v = [&](int c) {
 #pragma unroll
     for (int i = 0; i < NV; ++i)
-      vr[i] = ldg(vb + (size_t)c * U + (wave * 64 + i * 64 * kPrefillWaves) + frag_lane_unit(lane));
+      vr[i] = ldg(vb + (size_t)c * U + (wave * 64 + i * 64 * NW) + frag_lane_unit(lane));
   };
-  auto stage_k = [&](int buf) {
+  auto stage_k = [&](int buf, const uint4(&kr)[NV]) {
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-      const int u = tid + i * 64 * kPrefillWaves, key = u / KU, ku = u % KU;
+      const int u = tid + i * 64 * NW, key = u / KU, ku = u % KU;
       L[buf * U + key * KU + (ku ^ (key & 15))] = __builtin_bit_cast(u32x4, kr[i]);
     }
   };
@@ -88,8 +93,8 @@ __global__ __launch_bounds__(64 * kPrefillWaves, 2) void attn_prefill_wide_kerne
   // earlier request) are set to zero: their p is 0
   auto stage_v = [&](int c) {
     const int kc = c * kAttnChunk;
-    if (kc + kAttnChunk > last_all + 1) {
-      const int n0 = min(max(last_all + 1 - (kc + 4 * lg), 0), 4), n1 = min(max(last_all + 1 - (kc + 16 + 4 * lg), 0), 4);
+    if (kc + kAttnChunk > last + 1) {
+      const int n0 = min(max(last + 1 - (kc + 4 * lg), 0), 4), n1 = min(max(last + 1 - (kc + 16 + 4 * lg), 0), 4);
 #pragma unroll
       for (int i = 0; i < NV; ++i) {
         const uint4 a = keep_first<true>(make_uint4(vr[i].x, vr[i].y, 0, 0), n0);
@@ -98,45 +103,24 @@ __global__ __launch_bounds__(64 * kPrefillWaves, 2) void attn_prefill_wide_kerne
       }
     }
 #pragma unroll
-    for (int i = 0; i < NV; ++i) L[(3 + (c & 1)) * U + tid + i * 64 * kPrefillWaves] = __builtin_bit_cast(u32x4, vr[i]);
+    for (int i = 0; i < NV; ++i) L[(3 + (c & 1)) * U + tid + i * 64 * NW] = __builtin_bit_cast(u32x4, vr[i]);
   };
-  request_k(0);
-  request_v(0);
-
+  int k0 = 0, k1 = 1, k2 = 2;   // key buffers of this chunk, the next one and the one after
   Op2 q[KS];
   {
-    const float4* src = reinterpret_cast<const float4*>(p.q + (size_t)(rq.row_start + pos - rq.L0) * p.n_q * D + h * D + 8 * lg);
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      const float4 v[2] = {ldg(src + 8 * ks), ldg(src + 8 * ks + 1)};
-      q[ks] = split_op<true>(v);
-    }
-  }
-  int k0 = 0, k1 = 1, k2 = 2;   // key buffers of this chunk, the next one and the one after
-  stage_k(k0);
-  stage_v(0);
-  if (n_chunks > 1) {
-    request_k(1);
-    stage_k(k1);
+    uint4 kn[NV];   // the second chunk's keys
+    const int c1 = min(c_first + 1, c_end - 1);
+    request_k(c_first, kr);
+    request_v(c_first);
+    request_k(c1, kn);
+    load_q(q);
+    stage_k(k0, kr);
+    stage_v(c_first);
+    stage_k(k1, kn);
   }
   lds_sync();
 
-  // running maximum, sum and p v: of all spans so far, and of this span (an
-  // empty state joins as the identity)
-  float M = -INFINITY, S = 0.f, Ms, Ss;
-  float A[DT][4], As[DT][4];
-#pragma unroll
-  for (int t = 0; t < DT; ++t)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) A[t][i] = 0.f;
-  // attn_merge_coef for states that may be empty: 2^(-inf - 0) = 0
-  auto coef = [](float& M0, float& L0, float m, float l) {
-    const float Mn = fmaxf(M0, m), ref = Mn == -INFINITY ? 0.0f : Mn;
-    const MergeCoef k{exp2_hw(M0 - ref), exp2_hw(m - ref)};
-    L0 = __builtin_fmaf(L0, k.a, l * k.c);
-    M0 = Mn;
-    return k;
-  };
+  float Ms, Ss, As[DT][4];   // the span's maximum, sum and p v
   // A chunk's operands from the LDS in groups of two: KS groups of keys (the
   // two 16-key tiles of a k-step), then DT / 2 groups of values (two
   // dimension tiles).  Group n sits in slot n % 4 of f and is requested AHEAD
@@ -218,7 +202,7 @@ __global__ __launch_bounds__(64 * kPrefillWaves, 2) void attn_prefill_wide_kerne
       lw[e] = f2bf2(v0 - bf2f(hw[e]), v1 - __uint_as_float(hw[e] & 0xffff0000u));
     }
     const Op2 pp{make_uint4(hw[0], hw[1], hw[2], hw[3]), make_uint4(lw[0], lw[1], lw[2], lw[3])};
-    const MergeCoef k = coef(Ms, Ss, mx, sm);
+    const MergeCoef k = attn_coef0(Ms, Ss, mx, sm);
     __builtin_amdgcn_sched_barrier(0);
     // p v transposed (lane l: dimensions 16 t + 4 (l / 16) + i of row l % 16),
     // folded into the span's state one group late: p_hi v_hi, p_hi v_lo, p_lo v_hi
@@ -247,50 +231,144 @@ __global__ __launch_bounds__(64 * kPrefillWaves, 2) void attn_prefill_wide_kerne
     fold(DT / 2 - 1);
   };
 #pragma unroll
-  for (int n = 0; n < AHEAD; ++n) load(0, n);
-  for (int c0 = 0; c0 < n_chunks; c0 += kAttnSpanKeys / kAttnChunk) {
+  for (int n = 0; n < AHEAD; ++n) load(c_first, n);
+  for (int c0 = c_first; c0 < c_end; c0 += kAttnSpanKeys / kAttnChunk) {
     Ms = -INFINITY;
     Ss = 0.f;
 #pragma unroll
     for (int t = 0; t < DT; ++t)
 #pragma unroll
       for (int i = 0; i < 4; ++i) As[t][i] = 0.f;
-    const int c1 = min(c0 + kAttnSpanKeys / kAttnChunk, n_chunks);
+    const int c1 = min(c0 + kAttnSpanKeys / kAttnChunk, c_end);
     for (int c = c0; c < c1; ++c) {
-      if (c + 2 < n_chunks) request_k(c + 2);
-      if (c + 1 < n_chunks) request_v(c + 1);
+      if (c + 2 < c_end) request_k(c + 2, kr);
+      if (c + 1 < c_end) request_v(c + 1);
       chunk(c);   // past a tile's last key: every key hidden, the state unchanged
       // these buffers were last read in the chunk before, which every wave
       // has left
-      if (c + 2 < n_chunks) stage_k(k2);
-      if (c + 1 < n_chunks) stage_v(c + 1);
+      if (c + 2 < c_end) stage_k(k2, kr);
+      if (c + 1 < c_end) stage_v(c + 1);
       lds_sync();
       const int k = k0;
       k0 = k1;
       k1 = k2;
       k2 = k;
     }
-    // the span joins the others (a row that does not reach it: unchanged)
-    const MergeCoef ka = coef(M, S, Ms, Ss);
-#pragma unroll
-    for (int t = 0; t < DT; ++t)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) A[t][i] = attn_merge_acc(A[t][i], As[t][i], ka);
+    on_span(c0 / (kAttnSpanKeys / kAttnChunk), Ms, Ss, As);
   }
+}
+
+// The operands of one query row and head: this lane's share of every k-step.
+template <int D> __device__ __forceinline__ void attn_load_row(const AttnArgs& p, int row, int h, Op2 (&q)[D / 32]) {
+  const float4* src = reinterpret_cast<const float4*>(p.q + (size_t)row * p.n_q * D + h * D + 8 * ((threadIdx.x & 63) >> 4));
+#pragma unroll
+  for (int ks = 0; ks < D / 32; ++ks) {
+    const float4 v[2] = {ldg(src + 8 * ks), ldg(src + 8 * ks + 1)};
+    q[ks] = split_op<true>(v);
+  }
+}
+
+template <int D>
+__global__ __launch_bounds__(64 * kPrefillWaves, 2) void attn_prefill_wide_kernel(const AttnArgs p) {
+#pragma clang fp contract(off)
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  constexpr int DT = D / 16;
+  const ReqDesc rq = load_invariant(p.reqs);
+  const int lane = threadIdx.x & 63, lg = lane >> 4, lr = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int hpg = p.n_q / p.n_kv;
+  const int tiles = (rq.W + 15) / 16 * hpg, nw = (tiles + kPrefillWaves - 1) / kPrefillWaves;
+  const int g = blockIdx.x % p.n_kv, w = nw - 1 - blockIdx.x / p.n_kv;
+  const int T = min(w * kPrefillWaves + wave, tiles - 1);
+  const bool mine = w * kPrefillWaves + wave < tiles;
+  const int rt = T / hpg, h = g * hpg + (T - rt * hpg);
+  const int p0 = rq.L0 + rt * 16;                                 // position of the tile's first row
+  const int last = rq.L0 + min(rt * 16 + 15, rq.W - 1);           // ... and of its last one
+  const int pos = min(p0 + lr, last);                             // this lane's row (past the last: the last again)
+  const int last_all = rq.L0 + min(min((w + 1) * kPrefillWaves - 1, tiles - 1) / hpg * 16 + 15, rq.W - 1);
+
+  // the state of all spans so far (an empty one joins as the identity)
+  float M = -INFINITY, S = 0.f, A[DT][4];
+#pragma unroll
+  for (int t = 0; t < DT; ++t)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) A[t][i] = 0.f;
+  const int row = rq.row_start + pos - rq.L0;
+  attn_walk<D, kPrefillWaves>(
+      p, rq, g, p0, pos, last_all, 0, last_all / kAttnChunk + 1, smem, [&](Op2(&q)[D / 32]) { attn_load_row<D>(p, row, h, q); },
+      [&](int, float Ms, float Ss, const float(&As)[DT][4]) {
+        // a row that does not reach the span: unchanged
+        const MergeCoef ka = attn_coef0(M, S, Ms, Ss);
+#pragma unroll
+        for (int t = 0; t < DT; ++t)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) A[t][i] = attn_merge_acc(A[t][i], As[t][i], ka);
+      });
   if (!mine || p0 + lr > last) return;
 #pragma unroll
   for (int t = 0; t < DT; ++t) {
     float o[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) o[i] = A[t][i] / S;
-    store_act_run<true, false, 4>(p.out, p.out_plane,
-                                  frag_index<true>(rq.row_start + pos - rq.L0, h * D + 16 * t + 4 * lg, p.n_q * D), o);
+    store_act_run<true, false, 4>(p.out, p.out_plane, frag_index<true>(row, h * D + 16 * t + 4 * lg, p.n_q * D), o);
+  }
+}
+
+// Verification passes over long caches: work items (request, run of spans,
+// KV head, group of four row tiles), the rows of the query heads that share
+// the KV head packed head by head as in attn_group_kernel.  Each wave owns a
+// tile, so a run's keys and values are read once for up to 64 rows and a
+// span needs no exchange between waves (attn_group2_kernel: once per 16
+// rows, its four waves meeting twice per span).  Span states go to memory
+// for attn_merge_kernel.  A fixed grid takes the items in turn.
+template <int D>
+__global__ __launch_bounds__(64 * kSpanWaves, 2) void attn_spans_wide_kernel(const AttnArgs p, int n_reqs) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  constexpr int DT = D / 16, kRows = 16 * kSpanWaves, kChunks = kAttnSpanKeys / kAttnChunk;
+  const int lane = threadIdx.x & 63, lg = lane >> 4, lr = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int G = gridDim.x, hpg = p.n_q / p.n_kv;
+  const auto spans = [](const ReqDesc& rq) { return (rq.L0 + rq.W - 1) / kAttnSpanKeys + 1; };
+  const auto groups = [&](const ReqDesc& rq) { return p.n_kv * ((hpg * rq.W + kRows - 1) / kRows); };
+  const auto items = [&](const ReqDesc& rq, int R) { return groups(rq) * ((spans(rq) + R - 1) / R); };
+  int R, total;
+  attn_run_length(p.reqs, n_reqs, G, items, groups, R, total);
+  for (int t = xcd_contiguous(blockIdx.x, G); t < total; t += G) {
+    int u = t;
+    const int r = n_reqs == 1 ? 0 : find_request(p.reqs, n_reqs, u, [&](const ReqDesc& q) { return items(q, R); });
+    const ReqDesc rq = load_invariant(p.reqs + r);
+    const int ng = groups(rq), j = u / ng, v = u - j * ng;   // run j
+    const int per = ng / p.n_kv, g = v / per, b = v - g * per;
+    const AttnRows rows{g * hpg, rq.W, hpg * rq.W, b * kRows};
+    const int rr = 16 * wave + lr, i = rows.row(rr), h = rows.head(rr), row = rq.row_start + i;
+    const int last = rq.L0 + rq.W - 1, pos = rq.L0 + i;
+    const int c_first = j * R * kChunks, c_end = min(c_first + R * kChunks, last / kAttnChunk + 1);
+    attn_walk<D, kSpanWaves>(
+        p, rq, g, rq.L0, pos, last, c_first, c_end, smem, [&](Op2(&q)[D / 32]) { attn_load_row<D>(p, row, h, q); },
+        [&](int sp, float Ms, float Ss, const float(&As)[DT][4]) {
+          if (!rows.valid(rr) || pos < sp * kAttnSpanKeys) return;
+          const size_t o = ((size_t)row * p.n_q + h) * p.part_spans + sp;
+#pragma unroll
+          for (int t = 0; t < DT; ++t)
+            *gmem(reinterpret_cast<f4*>(p.pacc + o * D + 16 * t + 4 * lg)) = f4{As[t][0], As[t][1], As[t][2], As[t][3]};
+          if (lg == 0) *gmem(reinterpret_cast<f2*>(p.pml + o * 2)) = f2{Ms, Ss};
+        });
   }
 }
 
 hipError_t prepare_attn_prefill() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_prefill_wide_kernel<128>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, attn_wide_lds_bytes<128>());
+  auto allow = [](const void* k) {
+    return hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, attn_wide_lds_bytes<128>());
+  };
+  const hipError_t e = allow(reinterpret_cast<const void*>(&attn_prefill_wide_kernel<128>));
+  return e == hipSuccess ? allow(reinterpret_cast<const void*>(&attn_spans_wide_kernel<128>)) : e;
+}
+
+hipError_t launch_attn_spans(const AttnArgs& a, int n_reqs, int grid, hipStream_t s) {
+  if (a.head_dim == 128) attn_spans_wide_kernel<128><<<grid, 64 * kSpanWaves, attn_wide_lds_bytes<128>(), s>>>(a, n_reqs);
+  else if (a.head_dim == 64) attn_spans_wide_kernel<64><<<grid, 64 * kSpanWaves, attn_wide_lds_bytes<64>(), s>>>(a, n_reqs);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
 }
 
 hipError_t launch_attn_prefill(const AttnArgs& a, hipStream_t s) {

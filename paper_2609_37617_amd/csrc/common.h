@@ -399,6 +399,22 @@ template <class F> __device__ __forceinline__ int find_request(const ReqDesc* re
   return -1;
 }
 
+// The least run length R for which the requests' items(rq, R) fit G workgroups
+// (or stop shrinking: one run per group), and their total.
+template <class Items, class Groups>
+__device__ __forceinline__ void attn_run_length(const ReqDesc* reqs, int n_reqs, int G, Items&& items, Groups&& groups,
+                                                int& R, int& total) {
+  const auto sum = [&](auto&& f) { return n_reqs == 1 ? f(load_invariant(reqs)) : sum_requests(reqs, n_reqs, f); };
+  const auto n_items = [&](int r) { return sum([&](const ReqDesc& rq) { return items(rq, r); }); };
+  R = 1;
+  total = n_items(1);
+  if (total <= G) return;
+  const int least = sum([&](const ReqDesc& rq) { return groups(rq); });
+  R = (total + G - 1) / G;   // a run of R spans leaves at least total / R items
+  total = n_items(R);
+  while (total > G && total > least) total = n_items(++R);
+}
+
 // Workgroups are dealt to the 8 XCDs round-robin by linear index.  The
 // index v of the work a block takes: XCD j's blocks take one contiguous
 // range of v (the first n % 8 XCDs one more each), in dispatch order.

@@ -259,6 +259,9 @@ hipError_t launch_attention(bool bf16, const AttnArgs& a, int n_reqs, int max_bl
 // The prefill pass of a bf16 model (attn_prefill.hip): one request of a.M rows.
 hipError_t launch_attn_prefill(const AttnArgs& a, hipStream_t s);
 hipError_t prepare_attn_prefill();
+// Verification passes of bf16 models over long caches (same file): span states
+// for attn_merge_kernel, `grid` workgroups.
+hipError_t launch_attn_spans(const AttnArgs& a, int n_reqs, int grid, hipStream_t s);
 // n_rows = sum of the requests' W; counters: one per request, zero between launches.
 // Writes each verified row's greedy token, non-finite flag and top-2 margin,
 // and each request's outcome.

@@ -326,20 +326,8 @@ __device__ __forceinline__ void attn_group_items(const AttnArgs& p, int n_reqs, 
     const int ns = (rq.L0 + rq.W - 1) / kAttnSpanKeys + 1;
     return p.n_kv * blocks(rq) * ((ns + R - 1) / R);
   };
-  const auto n_items = [&](int R) {
-    if (n_reqs == 1) return items(load_invariant(p.reqs), R);
-    return sum_requests(p.reqs, n_reqs, [&](const ReqDesc& rq) { return items(rq, R); });
-  };
-  int R = 1, total = n_items(1);
-  if (total > G) {
-    // no run length gives fewer items than one run per block, nor, below
-    // total / G, few enough
-    const int least = n_reqs == 1 ? p.n_kv * blocks(load_invariant(p.reqs))
-                                  : sum_requests(p.reqs, n_reqs, [&](const ReqDesc& rq) { return p.n_kv * blocks(rq); });
-    R = (total + G - 1) / G;
-    total = n_items(R);
-    while (total > G && total > least) total = n_items(++R);
-  }
+  int R, total;
+  attn_run_length(p.reqs, n_reqs, G, items, [&](const ReqDesc& rq) { return p.n_kv * blocks(rq); }, R, total);
   for (int t = xcd_contiguous(blockIdx.x, G); t < total; t += G) {
     // item t: request r, then run j, KV head g, row block b
     int u = t;
@@ -563,7 +551,14 @@ static hipError_t attn_dispatch(const AttnArgs& a, int n_reqs, int max_blocks, b
   const long long rows = (long long)hpg * (a.M - n_reqs + 1);
   const long long items = (long long)n_reqs * a.n_kv * ((rows + 15) / 16) * ((max_blocks + kAttnSpan - 1) / kAttnSpan);
   const int cus = a.cus > 0 ? std::min(a.cus, kAttnGrid) : kAttnGrid;
-  if (items > cus && a.attn_rt == 0) {
+  // a slot of more than 16 spans whose requests have more than one row tile
+  // per KV head on average: a tile per wave, keys and values read once for
+  // four tiles.  One tile: the four waves share its chunks instead.
+  const bool wide = BF && !a.merge_last && a.attn_rt == 0 && (long long)hpg * a.M > 16ll * n_reqs;
+  if (wide) {
+    const hipError_t e = launch_attn_spans(a, n_reqs, 2 * cus, s);
+    if (e != hipSuccess) return e;
+  } else if (items > cus && a.attn_rt == 0) {
     const int grid2 = (int)std::min<long long>(2 * cus, (items + 7) / 8 * 8);
     attn_group2_kernel<BF, D><<<grid2, 256, attn_span_lds_bytes<BF, D, 1>(), s>>>(a, n_reqs);
   } else {
