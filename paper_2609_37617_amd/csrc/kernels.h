@@ -7,7 +7,7 @@
 // operand that is an activation is handed over as "planes": for bf16
 // models two bf16 planes hi = bf16(a), lo = bf16(a - hi) (a = hi + lo to
 // about 2^-17 relative), multiplied into the bf16 weights by two MFMAs;
-// for float32 models a single float32 plane.  A plane holds [kMaxRows][K]
+// for float32 models a single float32 plane.  A plane holds [rows][K]
 // elements in MFMA fragment order (frag_index in common.h): every 16-row
 // tile and k-step is one contiguous 1 KiB block, read by one wave with one
 // load.  The lo plane starts `plane` elements after the hi plane.
@@ -97,12 +97,13 @@ struct GemmArgs {
   int RB, CB, spu;       // wide path: row blocks, column blocks, slices per unit
   int rg_grid;           // staged path with row groups: row groups of 3, 2 tiles are
                          // used only if their grid reaches rg_grid workgroups (else 1 tile)
-  // A operand: activation planes [kMaxRows][K].  For A_NORM the planes
+  // A operand: activation planes [rows][K] (rows: the pass buffers', a_plane
+  // apart).  For A_NORM the planes
   // hold x * g (residual times RMSNorm gain) and the epilogue multiplies
   // row m by 1 / sqrt(sum(x^2) / K + eps) from the sum-of-squares partials.
   const void* A;
   long long a_plane;
-  const float* sumsq;    // A_NORM: per-pair partials [kMaxRows][K / 32]
+  const float* sumsq;    // A_NORM: per-pair partials [rows][K / 32]
   int n_norm_pairs;
   float eps;
   // split-K scratch
@@ -122,12 +123,12 @@ struct GemmArgs {
   const float* rope_cs;  // [kv_cap][head_dim/2][2] (cos, sin)
   const float* x;        // EPI_RESID: residual [M][N] read
   float* x_out;          // EPI_RESID: x + Y written (may equal x)
-  float* sumsq_out;      // EPI_RESID: per-pair partials [kMaxRows][N / 32]
+  float* sumsq_out;      // EPI_RESID: per-pair partials [rows][N / 32]
   const float* gain_next;// EPI_RESID: RMSNorm gain of the next consumer of x
   void* out;             // EPI_RESID: planes of x * gain_next; EPI_SWIGLU: planes of h
   long long out_plane;
   float* logits;         // EPI_ARGMAX: optional [M][N]
-  float* amax_val;       // EPI_ARGMAX: per-pair partials [kMaxRows][N / 32]: largest value,
+  float* amax_val;       // EPI_ARGMAX: per-pair partials [rows][N / 32]: largest value,
   float* amax_val2;      //   second-largest value,
   int* amax_idx;         //   lowest column holding the largest value
 };
@@ -175,7 +176,7 @@ struct AttnArgs {
                          // launches; [request][KV head][2 n_q / n_kv]: a request has at most 32 rows
                          // (max_k <= 31), so a KV head's rows fill at most that many 16-row blocks
   int merge_last;        // 1: the last item of a block merges its rows (no merge kernel)
-  void* out;             // planes [kMaxRows][n_q*d]
+  void* out;             // planes [rows][n_q*d]
   long long out_plane;
   int M;
   int attn_rt;           // row tiles per block of the verification kernel (0: chosen per launch)
