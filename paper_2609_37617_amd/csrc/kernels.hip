@@ -150,7 +150,7 @@ static void launch_direct(const GemmArgs& a, hipStream_t s) {
 // Balanced direct path: one workgroup per compute unit (the dynamic LDS
 // is at least kRangeMinLds, so two never share one), each streaming an
 // equal share of the (pair, split) units.  SL > 0: the variant with the
-// activation slice in registers (KS = 1, one row tile, KT = 4 SL).
+// activation slice in registers (KS = 1, KT = 4 SL; range_ra_slice).
 
 template <bool BF, int MT, int SL, int AM, int EPI>
 __global__ __launch_bounds__(256, 1) void gemm_range_kernel(const GemmArgs p) {
@@ -161,7 +161,7 @@ __global__ __launch_bounds__(256, 1) void gemm_range_kernel(const GemmArgs p) {
     gemm_range_direct<BF, MT, kRangePrefetch, AM, EPI, false>(p, p.M, smem, s_scale, s_flags, [] {});
   } else {
     constexpr int P = SL % kRangePrefetch == 0 ? kRangePrefetch : SL;
-    gemm_range_direct_ra<BF, P, SL, AM, EPI, false>(p, p.M, smem, s_scale, s_flags, [] {});
+    gemm_range_direct_ra<BF, MT, P, SL, AM, EPI, false>(p, p.M, smem, s_scale, s_flags, [] {});
   }
 }
 
@@ -180,9 +180,18 @@ static hipError_t launch_range(const GemmArgs& a, hipStream_t s) {
   if (lds < kRangeMinLds) lds = kRangeMinLds;
   const int sl = range_ra_slice<BF>(AM, EPI, a.MT, a.KS, a.KT);
   if constexpr (AM == A_NORM && (EPI == EPI_SWIGLU || EPI == EPI_ARGMAX)) {
-    if (sl == kRangeSL<BF>[0]) gemm_range_kernel<BF, 1, kRangeSL<BF>[0], AM, EPI><<<a.G, 256, lds, s>>>(a);
-    else if (sl == kRangeSL<BF>[1]) gemm_range_kernel<BF, 1, kRangeSL<BF>[1], AM, EPI><<<a.G, 256, lds, s>>>(a);
-    else if (sl == kRangeSL<BF>[2]) gemm_range_kernel<BF, 1, kRangeSL<BF>[2], AM, EPI><<<a.G, 256, lds, s>>>(a);
+    auto run = [&](auto c) {
+      constexpr int SL = decltype(c)::value;
+      if constexpr (BF)
+        if (a.MT == 2) {
+          gemm_range_kernel<BF, 2, SL, AM, EPI><<<a.G, 256, lds, s>>>(a);
+          return;
+        }
+      gemm_range_kernel<BF, 1, SL, AM, EPI><<<a.G, 256, lds, s>>>(a);
+    };
+    if (sl == kRangeSL<BF>[0]) run(std::integral_constant<int, kRangeSL<BF>[0]>());
+    else if (sl == kRangeSL<BF>[1]) run(std::integral_constant<int, kRangeSL<BF>[1]>());
+    else if (sl == kRangeSL<BF>[2]) run(std::integral_constant<int, kRangeSL<BF>[2]>());
   }
   if (!sl) {
     if (a.MT == 1) gemm_range_kernel<BF, 1, 0, AM, EPI><<<a.G, 256, lds, s>>>(a);
@@ -579,9 +588,13 @@ static hipError_t prepare_range() {
   hipError_t e = allow(reinterpret_cast<const void*>(&gemm_range_kernel<BF, 1, 0, AM, EPI>));
   if (e == hipSuccess) e = allow(reinterpret_cast<const void*>(&gemm_range_kernel<BF, 2, 0, AM, EPI>));
   if constexpr (AM == A_NORM && (EPI == EPI_SWIGLU || EPI == EPI_ARGMAX)) {
-    if (e == hipSuccess) e = allow(reinterpret_cast<const void*>(&gemm_range_kernel<BF, 1, kRangeSL<BF>[0], AM, EPI>));
-    if (e == hipSuccess) e = allow(reinterpret_cast<const void*>(&gemm_range_kernel<BF, 1, kRangeSL<BF>[1], AM, EPI>));
-    if (e == hipSuccess) e = allow(reinterpret_cast<const void*>(&gemm_range_kernel<BF, 1, kRangeSL<BF>[2], AM, EPI>));
+#define AS2D_R(mt, i) \
+  if (e == hipSuccess) e = allow(reinterpret_cast<const void*>(&gemm_range_kernel<BF, mt, kRangeSL<BF>[i], AM, EPI>));
+    AS2D_R(1, 0) AS2D_R(1, 1) AS2D_R(1, 2)
+    if constexpr (BF) {
+      AS2D_R(2, 0) AS2D_R(2, 1) AS2D_R(2, 2)
+    }
+#undef AS2D_R
   }
   return e;
 }

@@ -84,7 +84,7 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs& p, int M, const int* 
     if constexpr (SL > 0 && MT == 1 && AM == A_NORM && (EPI == EPI_SWIGLU || EPI == EPI_ARGMAX)) {
       if (range_ra_slice<BF>(AM, EPI, MT, p.KS, p.KT) == SL) {
         constexpr int P = SL % kRangePrefetch == 0 ? kRangePrefetch : SL;
-        gemm_range_direct_ra<BF, P, SL, AM, EPI, true>(p, M, smem, s_scale, s_flags, wait);
+        gemm_range_direct_ra<BF, 1, P, SL, AM, EPI, true>(p, M, smem, s_scale, s_flags, wait);
         ra = true;
       }
     }

@@ -27,8 +27,8 @@
 // at 1,904 rows, about the rate of a plain 8192^3 library product on this
 // device; one workgroup of 8 x 4 tiles per unit, with half the reads per
 // product, reached 0.7).  782 rows of the 7B shape, against passes of 144
-// rows through the staged path it replaces: gate/up 780 -> 425 us, down
-// 640 -> 234, QKV 354 -> 90, O 198 -> 65 us; at 84 rows (a fused batch)
+// rows through the staged path it replaces: gate/up 780 -> 432 us, down
+// 640 -> 240, QKV 354 -> 88, O 198 -> 69 us; at 84 rows (a fused batch)
 // 115 -> 90, 106 -> 61, 48 -> 27, 33 -> 21 us.  (QKV and O were 77 and 55,
 // 24 and 20 us with the three and two k-splits they had before the direct
 // path's plan left them whole; the direct path gained more than that.)
