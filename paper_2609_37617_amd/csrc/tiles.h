@@ -816,19 +816,30 @@ __device__ __forceinline__ void range_finish_units(const GemmArgs& p, int M, flo
   for (int j = 0; j < nu; ++j) {
     if (!s_flags[j]) continue;
     const int n = (u0 + j) / KS * kPairCols + (tid & 31);
-    float v[E::NE][kMaxSplits];
-#pragma unroll
-    for (int e = 0; e < E::NE; ++e)
-#pragma unroll
-      for (int sp = 0; sp < kMaxSplits; ++sp)
-        if (sp < KS) v[e][sp] = load_partial(&p.part[((size_t)sp * M + min(E::row_of(e), M - 1)) * p.N + n]);
+    // the splits in order, kWin of them in flight at a time (plans of the model
+    // shapes have up to 5): all kMaxSplits would take 128 registers with two
+    // row tiles, which the persistent kernel does not have beside the rest of
+    // a phase (212 to 276 bytes of scratch per lane; its pass at 0.5B, 17 to
+    // 32 rows, 6 layers: 415 - 469 us with them, 401 - 459 without)
+    constexpr int kWin = 4;
     float f[E::NE];
+#pragma unroll 1
+    for (int s0 = 0; s0 < KS; s0 += kWin) {
+      float v[E::NE][kWin];
+#pragma unroll
+      for (int e = 0; e < E::NE; ++e)
+#pragma unroll
+        for (int t = 0; t < kWin; ++t)
+          if (s0 + t < KS)
+            v[e][t] = load_partial(&p.part[((size_t)(s0 + t) * M + min(E::row_of(e), M - 1)) * p.N + n]);
+#pragma unroll
+      for (int e = 0; e < E::NE; ++e)
+#pragma unroll
+        for (int t = 0; t < kWin; ++t)
+          if (s0 + t < KS) f[e] = s0 + t == 0 ? v[e][t] : f[e] + v[e][t];
+    }
 #pragma unroll
     for (int e = 0; e < E::NE; ++e) {
-      f[e] = v[e][0];
-#pragma unroll
-      for (int sp = 1; sp < kMaxSplits; ++sp)
-        if (sp < KS) f[e] += v[e][sp];
       if constexpr (AM == A_NORM) f[e] *= s_scale[min(E::row_of(e), M - 1)];
     }
     epilogue(j, f);
