@@ -1164,7 +1164,7 @@ int as2d_load_weights(const as2d_config* cfg, const void* const* host, int32_t n
   // whole tiles; smaller units of the wide path take up to 128 MiB
   size_t part_elems = c->bf16 ? 32u << 20 : 0;
   for (const GemmPlan* p : {&c->p_qkv, &c->p_o, &c->p_gu, &c->p_down, &c->p_lm})
-    if (p->KS > 1) part_elems = std::max({part_elems, (size_t)p->KS * MR * p->N, wide_scratch_floats(p->N, (int)PR)});
+    if (p->KS > 1) part_elems = std::max({part_elems, (size_t)p->KS * MR * p->N, wide_scratch(p->N, (int)PR) / 4});
   CK(dalloc(c, &c->b.part, part_elems * 4));
   c->b.part_elems = part_elems;
   c->b.n_counters = split_counter_count(c, (int)PR);

@@ -18,18 +18,14 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "plan.h"
+
 namespace as2d {
 
 // GEMM tiling shared by the packer and the GEMM kernels.  The unit of
-// output columns is a tile pair: 32 columns, two 16-column MFMA tiles.
-constexpr int kWaves = 4;               // waves per workgroup
-constexpr int kPairCols = 32;           // columns of a tile pair
+// output columns is a tile pair (kPairCols): two 16-column MFMA tiles.
 constexpr int kMaxSlices = 16;          // ordered partial sums per k-split, at most
 constexpr int kPairsS = kWaves;         // tile pairs per workgroup, staged path
-constexpr int kMaxMTiles = 9;           // up to 144 rows per verification pass (and float32 prefill pass)
-constexpr int kPrefillRows = 8192;      // rows per prefill pass of bf16 models
-constexpr int kMaxRows = kMaxMTiles * 16;
-constexpr int kDirectMT = 2;            // row tiles of the direct path (up to 32 rows)
 constexpr int kStepRows = kDirectMT * 16;  // rows of a persistent-kernel pass
 constexpr int kAttnBlock = 64;          // keys per attention block (absolute positions)
 constexpr int kAttnSpan = 2;            // blocks per attention span (the first merge level)
@@ -240,10 +236,8 @@ hipError_t launch_embed(bool bf16, const RowDesc* rows, const PassDesc& put, int
 hipError_t launch_gemm(bool bf16, int amode, int epi, const GemmArgs& a, hipStream_t s);
 // The wide path of bf16 models (wide.hip): passes of more than kDirectMT row
 // tiles; a.part_bytes and a.n_counters bound the units it can split tiles
-// into.  wide_scratch_floats: what whole tiles of an N-column matrix with
-// k-splits need for passes of `rows` rows.
+// into (wide_plan).
 hipError_t launch_wide(int amode, int epi, const GemmArgs& a, hipStream_t s);
-size_t wide_scratch_floats(int N, int rows);
 hipError_t prepare_wide();
 int step_lds_bytes(int MT, int head_dim, int hidden);
 // Slice length of the register-resident balanced variant for a gate/up

@@ -1,5 +1,5 @@
-// Wide GEMMs of bf16 models (wide.h): kernels, the choice of tile and units
-// for a pass, and the launcher.
+// Wide GEMMs of bf16 models (wide.h): kernels and launcher.  The tile and
+// units of a pass are chosen by wide_plan (plan.h).
 #include "wide.h"
 
 namespace as2d {
@@ -23,67 +23,6 @@ __global__ __launch_bounds__(256, OCC) void gemm_wide_kernel(const GemmArgs p) {
   gemm_wide_tile<TM, TN, AH, AM, EPI>(p, rb, cb, unit, smem, s_scale, &s_flag);
 }
 
-// Tiles (TM x TN sixteens per wave, AH k-steps of weights ahead, OCC
-// workgroups per compute unit) and their times in microseconds, fitted to a
-// sweep of the 7B, 3B and 0.5B shapes' matrices at 48 to 1,904 rows (960
-// timings; the choice by this estimate is on average 1 % slower than the
-// best of the sweep, at most 19 %): `lat` per k-step of a workgroup that
-// waits for its own loads, `thr` per k-step and `fix` per unit of a compute
-// unit's throughput.
-struct WideTile {
-  int tm, tn, occ;
-  float lat, thr, fix;
-};
-constexpr WideTile kWideTiles[] = {
-    {4, 4, 2, 0.594f, 0.373f, 6.4f},
-    {3, 4, 2, 0.520f, 0.336f, 5.1f},
-    {2, 4, 2, 0.335f, 0.303f, 2.0f},
-    {2, 2, 4, 0.179f, 0.152f, 1.3f},
-};
-constexpr float kWideStart = 5.3f;     // launch to the first products, and the epilogue
-constexpr float kWideRecord = 2e-6f;   // per float of the records of split tiles
-
-struct WidePlan {
-  int tile = -1, RB = 0, CB = 0, spu = 0, grid = 0;
-};
-
-// The tile and the slices per unit for a pass of a.M rows: the least
-// estimated time over the tiles and, for each, whole tiles, splits and
-// slices as units (smaller units fill the device when a narrow matrix has
-// few tiles, and cost their records).  A tile's units run in rounds of
-// 256 x occ workgroups.
-static WidePlan wide_plan(const GemmArgs& a) {
-  constexpr int kCUs = 256;
-  WidePlan best;
-  float best_us = 0.f;
-  const int n_slices = a.KS * a.ns, last = a.KT - (a.KS - 1) * a.ktps;
-  for (int i = 0; i < (int)(sizeof kWideTiles / sizeof kWideTiles[0]); ++i) {
-    const WideTile& t = kWideTiles[i];
-    if ((a.N / 16) % (kWaves * t.tn)) continue;
-    const int RB = (a.MT + t.tm - 1) / t.tm, CB = a.N / (16 * kWaves * t.tn);
-    const long long tile_floats = (long long)t.tm * t.tn * 1024;   // of one tile's sums
-    for (const int spu : {n_slices, a.ns, 1}) {
-      if (spu == 1 && (a.ktps < a.ns || last < a.ns)) continue;   // empty slices
-      const int U = n_slices / spu;
-      const long long rec = U > 1 ? (long long)RB * CB * U * tile_floats : 0;
-      const long long scratch = U > 1 ? rec : a.KS > 1 ? (long long)RB * CB * tile_floats : 0;
-      if (scratch * 4 > a.part_bytes || (U > 1 && RB * CB > a.n_counters)) continue;
-      const long long wgs = (long long)RB * CB * U;
-      if (wgs > 0x7fffffff) continue;
-      const float ks = (float)a.KT / U, full = (float)wgs / kCUs;
-      const long long slots = (long long)kCUs * t.occ;
-      const float lat = (float)((wgs + slots - 1) / slots) * (ks * t.lat + kWideStart);
-      const float thr = (full < 4.f ? ceilf(full) : full + 0.5f) * (ks * t.thr + t.fix);
-      const float us = fmaxf(lat, thr) + kWideRecord * (float)rec;
-      if (best.tile < 0 || us < best_us) {
-        best_us = us;
-        best = WidePlan{i, RB, CB, spu, (int)wgs};
-      }
-    }
-  }
-  return best;
-}
-
 template <int TM, int TN, int AH, int OCC, int AM, int EPI>
 static hipError_t launch_tile(const GemmArgs& a, int grid, hipStream_t s) {
   gemm_wide_kernel<TM, TN, AH, OCC, AM, EPI><<<grid, 256, wide_lds_bytes<TM, TN>(), s>>>(a);
@@ -93,7 +32,7 @@ static hipError_t launch_tile(const GemmArgs& a, int grid, hipStream_t s) {
 template <int AM, int EPI>
 static hipError_t launch_epi(GemmArgs a, hipStream_t s) {
   if (a.MT < 1 || a.ns != kWaves || a.N % 128) return hipErrorInvalidValue;
-  const WidePlan w = wide_plan(a);
+  const WidePlan w = wide_plan(WideMatrix{a.N, a.KT, a.KS, a.ktps, a.ns}, a.MT, a.part_bytes, a.n_counters);
   a.RB = w.RB;
   a.CB = w.CB;
   a.spu = w.spu;
@@ -114,8 +53,6 @@ hipError_t launch_wide(int amode, int epi, const GemmArgs& a, hipStream_t s) {
 #undef AS2D_W
   return hipErrorInvalidValue;
 }
-
-size_t wide_scratch_floats(int N, int rows) { return (size_t)((rows + 15) / 16 + 3) * 16 * N; }
 
 template <int AM, int EPI>
 static hipError_t prepare_epi() {
