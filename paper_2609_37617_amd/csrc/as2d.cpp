@@ -107,7 +107,7 @@ struct as2d_ctx {
   int keep_logits = 0;
 
   // execution mode of verification passes (AS2D_EXEC_*) and the captured
-  // graphs: (mode, rows, requests, keep_logits) -> executable graph
+  // graphs: (mode, rows, requests, attention and keep_logits) -> executable graph
   int exec_mode = AS2D_EXEC_GRAPH;
   std::map<std::tuple<int, int, int, int>, hipGraphExec_t> graphs;
 
@@ -357,15 +357,44 @@ GemmArgs base_args(as2d_ctx* c, const GemmPlan& pl, const uint4* W, int M, const
 // kernels take base-2 exponentials of the scores).
 float attn_scale(int d) { return (float)(1.4426950408889634 / std::sqrt((double)d)); }
 
+// Caches of up to 16 spans: the span kernel merges (no second launch).
+bool merge_last(int part_spans) { return part_spans <= 16; }
+
+// Whether the attention of a verification pass (M rows of the n requests
+// reqs) gives each wave a row tile of its own (attn_spans_wide_kernel: keys
+// and values read once for four tiles) instead of a span's four chunks to the
+// four waves of a tile.  It does once the pass has more (span, KV head, row
+// tile) items than workgroups, two per compute unit: until then each item has
+// a workgroup, and a chunk per wave is the shorter chain.  One layer at 7B,
+// 512 workgroups, by items, chunk per wave against tile per wave: 9 rows of
+// 1,200 keys (160) 5.2 us shorter, of 4,000 (512) 6.5 us, of 7,564 (960)
+// equal; 17 rows of 2,000 keys (512) 5.9 us shorter, of 3,000 (768) 1.1 us
+// longer, of 7,564 (1,920) 14.5 us longer; 3B and 0.5B turn at the same count.
+// Slots of up to 16 spans merge in the span kernel instead; requests of one
+// row tile per KV head on average would leave three waves without one.  The
+// caches decide, not the slots, so a captured graph is kept for each answer.
+bool wave_tiles(const as2d_ctx* c, int M, const ReqDesc* reqs, int n, int part_spans) {
+  const as2d_config& g = c->cfg;
+  const int hpg = g.n_q_heads / g.n_kv_heads;
+  if (!c->bf16 || c->attn_rt || merge_last(part_spans) || (long long)hpg * M <= 16ll * n) return false;
+  long long items = 0;
+  for (int r = 0; r < n; ++r) {
+    const ReqDesc& q = reqs[r];
+    items += (long long)g.n_kv_heads * ((hpg * q.W + 15) / 16) * ((q.L0 + q.W - 1) / kAttnSpanKeys + 1);
+  }
+  return items > 2 * (c->grid_cus > 0 ? std::min(c->grid_cus, kAttnGrid) : kAttnGrid);
+}
+
 // Kernel launches of one forward pass over the rows and requests in the
 // device descriptors: n_att attention requests (d_reqs[0..n_att)), n_fin
 // finish requests (d_reqs[max_requests..)) covering fin_rows rows;
 // with_head = run the LM head and verification; prefill = a prefill pass
 // (one request, its rows in order): its head runs over the last row tile
 // only, whose first row becomes row 0 of the logits and arg-max buffers.  max_blocks bounds the
-// attention key blocks of any request (it sizes the attention grid).
+// attention key blocks of any request (it sizes the attention grid); tiles:
+// wave_tiles of the pass.
 int launch_pass(as2d_ctx* c, const PassBufs& B, int M, int n_att, int n_fin, int fin_rows, bool with_head,
-                int max_blocks, bool prefill) {
+                int max_blocks, bool prefill, bool tiles) {
   const as2d_config& g = c->cfg;
   hipStream_t s = c->stream;
   const bool bf = c->bf16;
@@ -417,12 +446,12 @@ int launch_pass(as2d_ctx* c, const PassBufs& B, int M, int n_att, int n_fin, int
       a.pacc = B.pacc;
       a.pml = B.pml;
       a.part_spans = B.part_spans;
-      // caches of up to 16 spans: the span kernel merges (no second launch)
-      a.merge_last = B.part_spans <= 16;
+      a.merge_last = merge_last(B.part_spans);
       a.attn_cnt = B.attn_cnt;
       a.out = B.attn;
       a.out_plane = B.attn_plane;
       a.M = M;
+      a.wave_tiles = tiles;
       a.attn_rt = c->attn_rt;
       a.cus = c->grid_cus;
       Timed t(c, K_ATTN);
@@ -653,19 +682,20 @@ int launch_persistent(as2d_ctx* c, int M, int n_att, int n_fin, int fin_rows) {
 // requests (fin_rows rows verified), captured on first use.  Kernel
 // arguments hold only pointers and sizes (the row and request descriptors
 // are read from device memory when the graph runs) and the attention grid
-// covers the slot capacity, so one graph serves every pass of that shape.
-int graph_for(as2d_ctx* c, int M, int n_att, int n_fin, int fin_rows, bool persistent, hipGraphExec_t* out) {
-  const auto key = std::make_tuple((int)persistent, M, n_att, c->keep_logits);
+// covers the slot capacity, so one graph (two with `tiles`, wave_tiles of the
+// pass) serves every pass of that shape.
+int graph_for(as2d_ctx* c, int M, int n_att, int n_fin, int fin_rows, bool persistent, bool tiles, hipGraphExec_t* out) {
+  const auto key = std::make_tuple((int)persistent, M, n_att, 2 * (int)tiles + c->keep_logits);
   auto it = c->graphs.find(key);
   if (it == c->graphs.end()) {
-    if (c->graphs.size() >= 64) {
+    if (c->graphs.size() >= 128) {
       for (auto& kv : c->graphs) hipGraphExecDestroy(kv.second);
       c->graphs.clear();
     }
     hipGraph_t gr = nullptr;
     HIP_TRY(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
     int rc = persistent ? launch_persistent(c, M, n_att, n_fin, fin_rows)
-                        : launch_pass(c, c->b, M, n_att, n_fin, fin_rows, true, c->n_blocks_cap, false);
+                        : launch_pass(c, c->b, M, n_att, n_fin, fin_rows, true, c->n_blocks_cap, false, tiles);
     hipError_t e = hipStreamEndCapture(c->stream, &gr);
     if (rc) {
       if (gr) hipGraphDestroy(gr);
@@ -683,9 +713,7 @@ int graph_for(as2d_ctx* c, int M, int n_att, int n_fin, int fin_rows, bool persi
 }
 
 // One forward pass over the rows and requests in h_rows / h_reqs (see
-// launch_pass).  Verification passes run as a captured HIP graph, one per
-// (rows, requests, keep_logits); the attention grid then covers the slot
-// capacity so that the graph stays valid as the cache grows.
+// launch_pass).  Verification passes run as a captured HIP graph (graph_for).
 int run_forward(as2d_ctx* c, int M, int n_att, int n_fin, bool with_head, bool verify_call = false) {
   const as2d_config& g = c->cfg;
   hipStream_t s = c->stream;
@@ -706,14 +734,15 @@ int run_forward(as2d_ctx* c, int M, int n_att, int n_fin, bool with_head, bool v
     HIP_TRY(c, hipMemcpyAsync(c->b.d_rows, c->h_rows, sizeof(RowDesc) * M, hipMemcpyHostToDevice, s));
     HIP_TRY(c, hipMemcpyAsync(c->b.d_reqs, c->h_reqs, sizeof(ReqDesc) * 2 * mr, hipMemcpyHostToDevice, s));
   }
+  const bool tiles = verify_call && !persistent && wave_tiles(c, M, c->h_reqs, n_att, c->b.part_spans);
   if (graph) {
     hipGraphExec_t ex = nullptr;
-    int rc = graph_for(c, M, n_att, n_fin, fin_rows, persistent, &ex);
+    int rc = graph_for(c, M, n_att, n_fin, fin_rows, persistent, tiles, &ex);
     if (rc) return rc;
     HIP_TRY(c, hipGraphLaunch(ex, s));
   } else {
     int rc = persistent ? launch_persistent(c, M, n_att, n_fin, fin_rows)
-                        : launch_pass(c, c->b, M, n_att, n_fin, fin_rows, with_head, max_blocks, !verify_call);
+                        : launch_pass(c, c->b, M, n_att, n_fin, fin_rows, with_head, max_blocks, !verify_call, tiles);
     if (rc) return rc;
   }
   if (persistent) HIP_TRY(c, hipMemcpyAsync(&c->h_err, c->perr, sizeof(int), hipMemcpyDeviceToHost, s));
@@ -741,9 +770,13 @@ int as2d_prepare_graphs(as2d_ctx* c, int32_t max_rows) {
   for (int M = 1; M <= max_rows; ++M) {
     const bool persistent = c->exec_mode == AS2D_EXEC_PERSISTENT && c->pers_ok && c->pers_fit && M <= kStepRows;
     if (persistent && !step_layers_for(c, M)) return fail(c, AS2D_ENOMEM, "persistent step arguments");
-    hipGraphExec_t ex = nullptr;
-    const int rc = graph_for(c, M, 1, 1, M, persistent, &ex);
-    if (rc) return rc;
+    // a short cache and a full slot, whose attention may differ
+    for (const int kv_len : {M, std::max(M, c->cfg.max_kv_len)}) {
+      const ReqDesc q{0, M, kv_len - M, 0};
+      hipGraphExec_t ex = nullptr;
+      const int rc = graph_for(c, M, 1, 1, M, persistent, !persistent && wave_tiles(c, M, &q, 1, c->b.part_spans), &ex);
+      if (rc) return rc;
+    }
   }
   return AS2D_OK;
 }
@@ -1351,7 +1384,7 @@ int as2d_verify_static(as2d_ctx* c, int32_t req, const int32_t* cands, int32_t k
   HIP_TRY(c, launch_fill_zero(S.counters, (int)(S.attn_cnt - S.counters) + mr * g.n_q_heads * 2, s));
   const int timing = c->timing;   // no event bracketing here (events are created on first use)
   c->timing = 0;
-  rc = launch_pass(c, S, M, 1, 1, M, true, n_blocks, false);
+  rc = launch_pass(c, S, M, 1, 1, M, true, n_blocks, false, wave_tiles(c, M, c->h_reqs, 1, S.part_spans));
   c->timing = timing;
   if (rc) return rc;
   HIP_TRY(c, hipStreamSynchronize(s));

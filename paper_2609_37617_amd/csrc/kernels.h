@@ -30,6 +30,7 @@ constexpr int kStepRows = kDirectMT * 16;  // rows of a persistent-kernel pass
 constexpr int kAttnBlock = 64;          // keys per attention block (absolute positions)
 constexpr int kAttnSpan = 2;            // blocks per attention span (the first merge level)
 constexpr int kAttnSpanKeys = kAttnSpan * kAttnBlock;
+constexpr int kAttnGrid = 256;          // compute units the span kernels fill at most (attn_group_kernel: one workgroup each)
 constexpr int kMaxSplits = 16;          // largest k-split count of a GEMM
 constexpr int kMaxUnits = 24;           // (pair, split) units per workgroup, balanced direct path
 constexpr int kMaxBlocks = 512;         // attention blocks per row (positions < 32768)
@@ -175,6 +176,7 @@ struct AttnArgs {
   void* out;             // planes [rows][n_q*d]
   long long out_plane;
   int M;
+  int wave_tiles;        // verification passes of bf16 models: a row tile per wave (attn_spans_wide_kernel)
   int attn_rt;           // row tiles per block of the verification kernel (0: chosen per launch)
   int cus;               // compute units the verification kernels may fill (the CU budget)
 };

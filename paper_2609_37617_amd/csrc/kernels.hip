@@ -315,7 +315,6 @@ hipError_t launch_gemm(bool bf16, int amode, int epi, const GemmArgs& a, hipStre
 // head, 16 rows) walks the spans in ascending order and merges them as it
 // goes, with the same arithmetic, so no partials go through memory.
 
-constexpr int kAttnGrid = 256;   // compute units the span kernels fill at most (attn_group_kernel: one workgroup each)
 
 // The items of a launch with blocks of RT row tiles.  LOWREG (RT = 1): a
 // workgroup within half the register file (two per compute unit), one span
@@ -560,11 +559,7 @@ static hipError_t attn_dispatch(const AttnArgs& a, int n_reqs, int max_blocks, b
   const long long rows = (long long)hpg * (a.M - n_reqs + 1);
   const long long items = (long long)n_reqs * a.n_kv * ((rows + 15) / 16) * ((max_blocks + kAttnSpan - 1) / kAttnSpan);
   const int cus = a.cus > 0 ? std::min(a.cus, kAttnGrid) : kAttnGrid;
-  // a slot of more than 16 spans whose requests have more than one row tile
-  // per KV head on average: a tile per wave, keys and values read once for
-  // four tiles.  One tile: the four waves share its chunks instead.
-  const bool wide = BF && !a.merge_last && a.attn_rt == 0 && (long long)hpg * a.M > 16ll * n_reqs;
-  if (wide) {
+  if (BF && a.wave_tiles) {
     const hipError_t e = launch_attn_spans(a, n_reqs, 2 * cus, s);
     if (e != hipSuccess) return e;
   } else if (items > cus && a.attn_rt == 0) {
