@@ -91,6 +91,15 @@ typedef struct {
  * hip_stream: the hipStream_t all work is ordered on (NULL: the library
  * creates its own).  The weights are repacked on the device into the tile
  * order the GEMM kernels stream.
+ * Device memory besides the weights, the KV slots (8 bytes per position,
+ * layer and KV dimension) and the scratch of verification passes: buffers
+ * for a prefill pass of R = min(8192, max_kv_len) rows of a bf16 model, about
+ * R (8 hidden + 8 n_q head_dim + 4 ffn) bytes, and its GEMMs' split sums
+ * (slots of 8,192 positions or more: 1.09 GB and 112 MiB for the 7B shape,
+ * 0.28 GB and 28 MiB for the 0.5B shape).  Where the device does not hold
+ * them, R is halved until it does, down to 144 rows: prefills then run in
+ * more passes, with the same results.  AS2D_PREFILL_ROWS in the environment
+ * lowers R.
  */
 int as2d_load_weights(const as2d_config* cfg, const void* const* host_tensors, int32_t n_tensors,
                       void* hip_stream, as2d_ctx** out);

@@ -983,6 +983,72 @@ size_t static_layout(const as2d_ctx* c, int n_blocks, char* base, PassBufs* S) {
   return off;
 }
 
+// The buffers that grow with the rows of a pass (x, q, the activation planes,
+// row sums, split sums and counters, row descriptors), and with them the rows
+// of a prefill pass: up to kPrefillRows for bf16 models (their attention and
+// GEMMs fill the device best in one pass), fewer if the device's memory does
+// not hold them, and at least a verification pass's.  AS2D_PREFILL_ROWS lowers
+// the first choice.  A smaller pass changes no result.
+int alloc_pass(as2d_ctx* c) {
+  const as2d_config& g = c->cfg;
+  const size_t H = g.hidden, F = g.ffn, QD = (size_t)g.n_q_heads * g.head_dim;
+  PassBufs& B = c->b;
+  int want = c->bf16 ? std::min(kPrefillRows, (g.max_kv_len + 15) / 16 * 16) : kMaxRows;
+  if (const int v = env_int("AS2D_PREFILL_ROWS", 0); v > 0) want = std::min(want, (v + 15) / 16 * 16);
+  const size_t first = c->allocs.size();
+  // buffers for passes of up to R rows
+  auto attempt = [&](size_t R) -> int {
+    const GemmPlan* plans[] = {&c->p_qkv, &c->p_o, &c->p_gu, &c->p_down, &c->p_lm};
+    PassMatrix m[5];
+    size_t part = 0;
+    for (int i = 0; i < 5; ++i) {
+      const GemmPlan& p = *plans[i];
+      // a prefill's head runs over one row tile (launch_pass)
+      m[i] = PassMatrix{WideMatrix{p.N, p.KT, p.KS, p.ktps, p.ns}, i == 4 ? kMaxRows : (int)R};
+      if (!c->bf16 && p.KS > 1) part = std::max(part, (size_t)p.KS * kMaxRows * p.N * 4);
+    }
+    B.n_counters = split_counter_count(c, (int)R);
+    if (c->bf16) part = (size_t)pass_part_bytes(m, 5, B.n_counters);
+    B.part_elems = part / 4;
+    // activation planes: two bf16 planes or one float32 plane, 4 bytes per element either way
+    if (c->bf16) {
+      B.xg_plane = (long long)(R * H);
+      B.attn_plane = (long long)(R * QD);
+      B.h_plane = (long long)(R * F);
+    }
+    int rc = AS2D_OK;
+    auto take = [&](auto** p, size_t bytes) { if (!rc) rc = dalloc(c, p, bytes); };
+    take(&B.x, R * H * 4);
+    take(&B.q, R * QD * 4);
+    take(&B.xg, R * H * 4);
+    take(&B.attn, R * QD * 4);
+    take(&B.hbuf, R * F * 4);
+    take(&B.sumsq, (H / kPairCols) * R * 4);
+    take(&B.part, part);
+    take(&B.counters, (size_t)B.n_counters * 4);
+    take(&B.d_rows, sizeof(RowDesc) * R);
+    if (!rc && R > kMaxRows) {   // leave room for a prefill's audio rows
+      void* p = nullptr;
+      if (hipMalloc(&p, (size_t)g.max_kv_len * H * c->es) == hipSuccess) hipFree(p);
+      else rc = AS2D_ENOMEM;
+    }
+    return rc;
+  };
+  int rc = AS2D_OK;
+  const int rows = rows_that_fit(std::max(want, kMaxRows), kMaxRows, [&](int R) {
+    rc = attempt((size_t)R);
+    if (!rc) return true;
+    for (; c->allocs.size() > first; c->allocs.pop_back()) hipFree(c->allocs.back());
+    (void)hipGetLastError();   // the next launch must not report this allocation's error
+    return false;
+  });
+  if (!rows) return rc;
+  c->err.clear();
+  c->prefill_rows = std::min(want, rows);
+  HIP_TRY(c, hipMemsetAsync(B.counters, 0, (size_t)B.n_counters * 4, c->stream));
+  return AS2D_OK;
+}
+
 }  // namespace
 
 // ===========================================================================
@@ -1165,26 +1231,10 @@ int as2d_load_weights(const as2d_config* cfg, const void* const* host, int32_t n
   CK(dalloc(c, &c->kc, kv_bytes));
   CK(dalloc(c, &c->vc, kv_bytes));
 
-  // activations and scratch, sized for the largest pass: MR rows of a
-  // verification pass, PR of any pass (a prefill of a bf16 model takes up to
-  // kPrefillRows rows at a time)
+  // scratch of verification passes (MR rows); alloc_pass, last, has what grows with a prefill's rows
   const int MR = kMaxRows;
-  c->prefill_rows = c->bf16 ? std::min(kPrefillRows, (g.max_kv_len + 15) / 16 * 16) : MR;
-  const size_t PR = std::max(c->prefill_rows, MR);
   c->n_blocks_cap = (g.max_kv_len + kAttnBlock - 1) / kAttnBlock;
-  CK(dalloc(c, &c->b.x, PR * H * 4));
-  CK(dalloc(c, &c->b.q, PR * nq * d * 4));
-  // activation planes: two bf16 planes or one float32 plane, 4 bytes per element either way
-  CK(dalloc(c, &c->b.xg, PR * H * 4));
-  CK(dalloc(c, &c->b.attn, PR * nq * d * 4));
-  CK(dalloc(c, &c->b.hbuf, PR * F * 4));
-  if (c->bf16) {
-    c->b.xg_plane = (long long)PR * H;
-    c->b.attn_plane = (long long)PR * nq * d;
-    c->b.h_plane = (long long)PR * F;
-  }
   CK(dalloc(c, &c->b.logits, (size_t)MR * V * 4));
-  CK(dalloc(c, &c->b.sumsq, (H / kPairCols) * PR * 4));
   CK(dalloc(c, &c->b.amax_val, (size_t)(V / kPairCols) * MR * 4));
   CK(dalloc(c, &c->b.amax_val2, (size_t)(V / kPairCols) * MR * 4));
   CK(dalloc(c, &c->b.row_margin, (size_t)MR * 4));
@@ -1193,16 +1243,6 @@ int as2d_load_weights(const as2d_config* cfg, const void* const* host, int32_t n
   CK(dalloc(c, &c->b.row_bad, (size_t)MR * 4));
   CK(dalloc(c, &c->b.fin_counters, (size_t)g.max_requests * 4));
   HIP_TRY(c, hipMemsetAsync(c->b.fin_counters, 0, (size_t)g.max_requests * 4, c->stream));
-  // split-K partials: of whole verification passes, and on the wide path of
-  // whole tiles; smaller units of the wide path take up to 128 MiB
-  size_t part_elems = c->bf16 ? 32u << 20 : 0;
-  for (const GemmPlan* p : {&c->p_qkv, &c->p_o, &c->p_gu, &c->p_down, &c->p_lm})
-    if (p->KS > 1) part_elems = std::max({part_elems, (size_t)p->KS * MR * p->N, wide_scratch(p->N, (int)PR) / 4});
-  CK(dalloc(c, &c->b.part, part_elems * 4));
-  c->b.part_elems = part_elems;
-  c->b.n_counters = split_counter_count(c, (int)PR);
-  CK(dalloc(c, &c->b.counters, (size_t)c->b.n_counters * 4));
-  HIP_TRY(c, hipMemsetAsync(c->b.counters, 0, (size_t)c->b.n_counters * 4, c->stream));
   HIP_TRY(c, prepare_kernels());
   {
     // the static scratch of as2d_verify_static: its address on this device
@@ -1250,7 +1290,6 @@ int as2d_load_weights(const as2d_config* cfg, const void* const* host, int32_t n
   CK(dalloc(c, &c->b.pml, spans_cap * MR * nq * 2 * 4));
   CK(dalloc(c, &c->b.attn_cnt, (size_t)g.max_requests * nq * 2 * 4));
   HIP_TRY(c, hipMemsetAsync(c->b.attn_cnt, 0, (size_t)g.max_requests * nq * 2 * 4, c->stream));
-  CK(dalloc(c, &c->b.d_rows, sizeof(RowDesc) * PR));
   CK(dalloc(c, &c->b.d_reqs, sizeof(ReqDesc) * 2 * g.max_requests));
   CK(dalloc(c, &c->b.d_out, sizeof(StepOut) * g.max_requests));
 
@@ -1267,7 +1306,9 @@ int as2d_load_weights(const as2d_config* cfg, const void* const* host, int32_t n
     CK(dalloc(c, &c->rope_cs, cs.size() * 4));
     HIP_TRY(c, hipMemcpy(c->rope_cs, cs.data(), cs.size() * 4, hipMemcpyHostToDevice));
   }
-  if (hipHostMalloc((void**)&c->h_rows, sizeof(RowDesc) * PR, 0) != hipSuccess ||
+  CK(alloc_pass(c));
+  const size_t rows = std::max(c->prefill_rows, MR);
+  if (hipHostMalloc((void**)&c->h_rows, sizeof(RowDesc) * rows, 0) != hipSuccess ||
       hipHostMalloc((void**)&c->h_reqs, sizeof(ReqDesc) * 2 * g.max_requests, 0) != hipSuccess ||
       hipHostMalloc((void**)&c->h_out, sizeof(StepOut) * g.max_requests, 0) != hipSuccess ||
       hipHostMalloc((void**)&c->h_tok, sizeof(int) * MR, 0) != hipSuccess ||

@@ -16,6 +16,7 @@ constexpr int kMaxMTiles = 9;           // up to 144 rows per verification pass 
 constexpr int kMaxRows = kMaxMTiles * 16;
 constexpr int kPrefillRows = 8192;      // rows per prefill pass of bf16 models, at most
 constexpr int kDirectMT = 2;            // row tiles of the direct path (up to 32 rows)
+constexpr long long kWideSplitBytes = 128ll << 20;   // records the wide path may split tiles into, whatever the model
 
 // ---------------------------------------------------------------------------
 // Wide GEMMs
@@ -92,6 +93,42 @@ inline WidePlan wide_plan(const WideMatrix& a, int MT, long long part_bytes, int
     }
   }
   return best;
+}
+
+// ---------------------------------------------------------------------------
+// Pass buffers
+
+// A matrix and the rows of the passes that read it, at most.
+struct PassMatrix {
+  WideMatrix w;
+  int rows;
+};
+
+// Bytes of split sums that the passes of a bf16 model need: what the direct
+// path's k-splits and the wide path's chosen plans write.  The plans are
+// chosen within kWideSplitBytes, or what whole tiles take if that is more;
+// a launch that is given the result as its bound chooses the same ones.
+inline long long pass_part_bytes(const PassMatrix* m, int n, int n_counters) {
+  long long limit = kWideSplitBytes, need = 0;
+  for (int i = 0; i < n; ++i)
+    if (m[i].w.KS > 1) {
+      need = std::max(need, (long long)m[i].w.KS * kDirectMT * 16 * m[i].w.N * 4);
+      limit = std::max(limit, (long long)wide_scratch(m[i].w.N, m[i].rows));
+    }
+  for (int i = 0; i < n; ++i)
+    for (int MT = kDirectMT + 1; MT <= (m[i].rows + 15) / 16; ++MT)
+      need = std::max(need, wide_plan(m[i].w, MT, limit, n_counters).scratch);
+  return need;
+}
+
+// Rows per pass for which fits(rows) holds: `rows`, or else half as many at a
+// time (whole row tiles), down to `least`.  0: not even that.
+template <class Fits> inline int rows_that_fit(int rows, int least, Fits&& fits) {
+  for (;;) {
+    if (fits(rows)) return rows;
+    if (rows <= least) return 0;
+    rows = std::max(least, (rows / 2 + 15) / 16 * 16);
+  }
 }
 
 }  // namespace as2d

@@ -2,7 +2,10 @@
 without a device: a small C++ shim built with the host compiler exports them.
 
 Wide GEMM units write their sums as records that the kernel reaches by 32-bit
-byte offsets below 2^31: no plan may need more, whatever the scratch."""
+byte offsets below 2^31: no plan may need more, whatever the scratch.  The
+scratch a context reserves is what the chosen plans write, and no plan changes
+for it; where the memory is short, passes get smaller instead of the load
+failing."""
 import ctypes
 import os
 import random
@@ -23,6 +26,17 @@ extern "C" void plan(const int* m, int MT, long long part_bytes, int n_counters,
   out[1] = p.tile < 0 ? 0 : kWideTiles[p.tile].tn;
   out[2] = p.RB; out[3] = p.CB; out[4] = p.spu; out[5] = p.grid; out[6] = p.scratch;
 }
+extern "C" long long part_bytes(const int* m, int n, int n_counters) {   // n matrices: a WideMatrix and its rows
+  PassMatrix a[8];
+  for (int i = 0; i < n; ++i, m += 6) a[i] = PassMatrix{WideMatrix{m[0], m[1], m[2], m[3], m[4]}, m[5]};
+  return pass_part_bytes(a, n, n_counters);
+}
+extern "C" int fit(int rows, int least, int most, int* tried) {
+  int n = 0;
+  const int r = rows_that_fit(rows, least, [&](int x) { tried[n++] = x; return x <= most; });
+  tried[n] = 0;
+  return r;
+}
 """
 
 
@@ -33,7 +47,9 @@ def lib(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I",
                     os.path.join(ROOT, "paper_2609_37617_amd", "csrc"), str(d / "shim.cpp"), "-o", str(d / "shim.so")],
                    check=True)
-    return ctypes.CDLL(str(d / "shim.so"))
+    lib = ctypes.CDLL(str(d / "shim.so"))
+    lib.part_bytes.restype = ctypes.c_longlong
+    return lib
 
 
 def wide(lib, matrix, MT, part_bytes, n_counters):
@@ -84,3 +100,42 @@ def test_plans_of_the_models(lib):
                 for MT in [3, 4, 5, 9] + [rng.randint(3, 512) for _ in range(8)]:
                     m = matrix(N, K, KS)
                     check(wide(lib, m, MT, 128 << 20 if KS == 1 else 1 << 33, N * 17), m, MT)
+
+
+def matrices(s, splits, rows):
+    """The five matrices of a model with the given k-splits; the head's passes have up to 144 rows."""
+    dims = ((s.qkv_out, s.hidden), (s.hidden, s.n_q_heads * s.head_dim), (2 * s.ffn, s.hidden),
+            (s.hidden, s.ffn), (s.vocab, s.hidden))
+    return [matrix(N, K, KS) + (rows if i < 4 else 144,) for i, ((N, K), KS) in enumerate(zip(dims, splits))]
+
+
+@pytest.mark.parametrize("shape,splits", [(TINY_BF16, (1, 1, 1, 1, 1)), (QWEN05B, (1, 1, 1, 5, 1)),
+                                          (QWEN3B, (1, 1, 1, 4, 1)), (QWEN7B, (1, 1, 1, 2, 1)), (QWEN7B, (3, 2, 1, 2, 4))],
+                         ids=lambda v: getattr(v, "name", str(v)))
+@pytest.mark.parametrize("rows", [144, 800, 8192])
+def test_split_scratch_is_what_the_plans_write(lib, shape, splits, rows):
+    ms = matrices(shape, splits, rows)
+    n_counters = max(N // 128 * max(9, (rows + 31) // 32) for N, *_ in ms)
+    flat = [v for m in ms for v in m]
+    part = lib.part_bytes((ctypes.c_int * len(flat))(*flat), len(ms), n_counters)
+    limit = max([128 << 20] + [((m[5] + 15) // 16 + 3) * 64 * m[0] for m in ms if m[2] > 1])
+    used = max([m[2] * 32 * m[0] * 4 for m in ms if m[2] > 1], default=0)
+    for m in ms:
+        for MT in range(3, (m[5] + 15) // 16 + 1):
+            p = wide(lib, m[:5], MT, limit, n_counters)
+            assert p == wide(lib, m[:5], MT, part, n_counters)   # the same plan within what is reserved
+            used = max(used, p["scratch"])
+    assert part == used <= limit
+
+
+def test_passes_shrink_to_the_memory(lib):
+    def fit(rows, least, most):
+        tried = (ctypes.c_int * 32)()
+        r = lib.fit(rows, least, most, tried)
+        return r, list(tried)[:list(tried).index(0)]
+    assert fit(8192, 144, 8192) == (8192, [8192])
+    assert fit(8192, 144, 3000) == (2048, [8192, 4096, 2048])
+    assert fit(8192, 144, 150) == (144, [8192, 4096, 2048, 1024, 512, 256, 144])
+    assert fit(1040, 144, 300) == (272, [1040, 528, 272])
+    assert fit(144, 144, 143) == (0, [144])
+    assert fit(8192, 144, 100)[0] == 0
