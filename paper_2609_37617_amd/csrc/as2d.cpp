@@ -1358,9 +1358,7 @@ int as2d_prefill_kv(as2d_ctx* c, int32_t req, const void* audio, int32_t n_audio
     }
     HIP_TRY(c, hipMemcpyAsync(c->audio, audio, bytes, hipMemcpyHostToDevice, c->stream));
   }
-  // passes of about the same number of whole row tiles
-  const int passes = (total + c->prefill_rows - 1) / c->prefill_rows;
-  const int chunk = ((total + passes - 1) / passes + 15) / 16 * 16;
+  const int chunk = pass_rows(total, c->prefill_rows, c->bf16);
   const int mr = g.max_requests;
   for (int r0 = 0; r0 < total; r0 += chunk) {
     const int M = std::min(chunk, total - r0);

@@ -121,6 +121,21 @@ inline long long pass_part_bytes(const PassMatrix* m, int n, int n_counters) {
   return need;
 }
 
+// Rows of each pass but the last of a prefill of `total` rows in passes of up
+// to `most` (whole row tiles): passes of about the same size, but full ones
+// where float32 models then leave the last pass to the direct path.  Equal
+// passes against full ones, 0.5B widths in float32 (3 layers): 145, 161, 290,
+// 320, 433 rows 774, 820, 1,338, 1,415, 1,916 / 676, 726, 1,189, 1,275,
+// 1,716 us (the tiny model the same way); 177 rows, which leave 33 to the
+// staged path, 857 / 1,035, 3B widths 225 and 512 rows (81 and 80 left) 1,397
+// and 2,918 / 1,516 and 3,223.
+inline int pass_rows(int total, int most, bool bf16) {
+  const int left = total % most;
+  if (!bf16 && total > most && left > 0 && left <= kDirectMT * 16) return most;
+  const int passes = (total + most - 1) / most;
+  return ((total + passes - 1) / passes + 15) / 16 * 16;
+}
+
 // Rows per pass for which fits(rows) holds: `rows`, or else half as many at a
 // time (whole row tiles), down to `least`.  0: not even that.
 template <class Fits> inline int rows_that_fit(int rows, int least, Fits&& fits) {

@@ -31,6 +31,7 @@ extern "C" long long part_bytes(const int* m, int n, int n_counters) {   // n ma
   for (int i = 0; i < n; ++i, m += 6) a[i] = PassMatrix{WideMatrix{m[0], m[1], m[2], m[3], m[4]}, m[5]};
   return pass_part_bytes(a, n, n_counters);
 }
+extern "C" int rows_per_pass(int total, int most, int bf16) { return pass_rows(total, most, bf16); }
 extern "C" int fit(int rows, int least, int most, int* tried) {
   int n = 0;
   const int r = rows_that_fit(rows, least, [&](int x) { tried[n++] = x; return x <= most; });
@@ -139,3 +140,20 @@ def test_passes_shrink_to_the_memory(lib):
     assert fit(1040, 144, 300) == (272, [1040, 528, 272])
     assert fit(144, 144, 143) == (0, [144])
     assert fit(8192, 144, 100)[0] == 0
+
+
+@pytest.mark.parametrize("bf16,mosts", [(0, (144, 48, 16)), (1, (8192, 2048, 144, 16))])
+def test_passes_of_a_prefill(lib, bf16, mosts):
+    """Whole row tiles of at most `most` rows, as few passes as it allows, and
+    none without rows."""
+    for most in mosts:
+        for total in list(range(1, 700)) + [2047, 2048, 2049, 8191, 8192, 8193, 16032, 32767, 32768]:
+            rows = lib.rows_per_pass(total, most, bf16)
+            assert 0 < rows <= most and rows % 16 == 0
+            assert -(-total // rows) == -(-total // most), (total, most)
+
+
+def test_float32_passes_leave_a_few_rows_to_the_direct_path(lib):
+    # a remainder of up to 32 rows stays the last pass (145 rows: 144 and 1, not 80 and 65)
+    assert [lib.rows_per_pass(n, 144, 0) for n in (144, 145, 176, 177, 289, 320, 321, 433)] == [144, 144, 144, 96, 144, 144, 112, 144]
+    assert [lib.rows_per_pass(n, 8192, 1) for n in (145, 8192, 8193, 8413)] == [160, 8192, 4112, 4208]
