@@ -1308,11 +1308,12 @@ int as2d_load_weights(const as2d_config* cfg, const void* const* host, int32_t n
   }
   CK(alloc_pass(c));
   const size_t rows = std::max(c->prefill_rows, MR);
-  if (hipHostMalloc((void**)&c->h_rows, sizeof(RowDesc) * rows, 0) != hipSuccess ||
-      hipHostMalloc((void**)&c->h_reqs, sizeof(ReqDesc) * 2 * g.max_requests, 0) != hipSuccess ||
-      hipHostMalloc((void**)&c->h_out, sizeof(StepOut) * g.max_requests, 0) != hipSuccess ||
-      hipHostMalloc((void**)&c->h_tok, sizeof(int) * MR, 0) != hipSuccess ||
-      hipHostMalloc((void**)&c->h_margin, sizeof(float) * MR, 0) != hipSuccess) {
+  // read and written by kernels without copies (embed_kernel, finish_kernel): coherent
+  // whatever the runtime's default for pinned memory is
+  auto pinned = [](auto** p, size_t bytes) { return hipHostMalloc((void**)p, bytes, hipHostMallocCoherent) == hipSuccess; };
+  if (!pinned(&c->h_rows, sizeof(RowDesc) * rows) || !pinned(&c->h_reqs, sizeof(ReqDesc) * 2 * g.max_requests) ||
+      !pinned(&c->h_out, sizeof(StepOut) * g.max_requests) || !pinned(&c->h_tok, sizeof(int) * MR) ||
+      !pinned(&c->h_margin, sizeof(float) * MR)) {
     return fail(c, AS2D_ENOMEM, "pinned host buffers");
   }
   memset(c->h_reqs, 0, sizeof(ReqDesc) * 2 * g.max_requests);
