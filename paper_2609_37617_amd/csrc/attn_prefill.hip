@@ -4,9 +4,9 @@
 // A workgroup of eight waves serves one KV head: each wave owns one tile of
 // 16 rows of one of its query heads and walks the keys chunk by chunk (32
 // keys) in ascending order, so the fold over chunks and spans stays in its
-// registers.  The chunk's keys and values are read once per workgroup, two
-// chunks buffered in LDS, the next one requested before the current one is
-// used.  Tiles are numbered row tile first, query head second, so a
+// registers.  The chunk's keys and values are read once per workgroup into
+// LDS (three key buffers, two of values), the next keys two chunks ahead, the
+// next values one.  Tiles are numbered row tile first, query head second, so a
 // workgroup's tiles see about the same keys; the rows with the most keys
 // start first.
 //

@@ -212,7 +212,7 @@ constexpr int kStagedGroupMT = 3;
 // Row groups (up to three row tiles) fit four workgroups per compute unit,
 // or two with two pairs per wave (NPW = 2: a pair group of 8 pairs); more
 // rows need the whole register file.
-template <bool BF, int MT, int AM, int EPI, int NPW = 1>
+template <int MT, int AM, int EPI, int NPW = 1>
 __global__ __launch_bounds__(256, NPW > 1 ? 2 : MT <= kStagedGroupMT ? 4 : 1) void gemm_staged_kernel(const GemmArgs p,
                                                                                                     const int RG) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -221,13 +221,12 @@ __global__ __launch_bounds__(256, NPW > 1 ? 2 : MT <= kStagedGroupMT ? 4 : 1) vo
   const int v = RG > 1 ? xcd_contiguous(blockIdx.x, gridDim.x) : (int)blockIdx.x;
   const int rg = v % RG, t = v / RG;
   const int group = t / p.KS, split = t - group * p.KS;
-  gemm_tile_staged<BF, MT, AM, EPI, false, (MT <= kStagedGroupMT), NPW>(p, p.M, group, split, smem, s_scale, &s_flag,
-                                                                        rg * MT, group * RG + rg);
+  gemm_tile_staged<MT, AM, EPI, (MT <= kStagedGroupMT), NPW>(p, p.M, group, split, smem, s_scale, &s_flag, rg * MT,
+                                                             group * RG + rg);
 }
 
 template <int AM, int EPI>
 static hipError_t launch_staged(const GemmArgs& a, hipStream_t s) {
-  constexpr bool BF = false;
   const int pairs = a.N / kPairCols;
   if (pairs % kPairsS) return hipErrorInvalidValue;
   const int base = (pairs / kPairsS) * a.KS;
@@ -245,17 +244,17 @@ static hipError_t launch_staged(const GemmArgs& a, hipStream_t s) {
     if (g == 3 && pairs % (2 * kPairsS) == 0) {
       // two pairs per wave: each staged activation fragment feeds twice the
       // weights, half the workgroups
-      gemm_staged_kernel<BF, 3, AM, EPI, 2>
-          <<<base / 2 * RG, 256, gemm_staged_lds_bytes<BF, 3, 2>(), s>>>(a, RG);
-    } else if (g == 3) gemm_staged_kernel<BF, 3, AM, EPI><<<base * RG, 256, gemm_staged_lds_bytes<BF, 3>(), s>>>(a, RG);
-    else if (g == 2) gemm_staged_kernel<BF, 2, AM, EPI><<<base * RG, 256, gemm_staged_lds_bytes<BF, 2>(), s>>>(a, RG);
-    else gemm_staged_kernel<BF, 1, AM, EPI><<<base * RG, 256, gemm_staged_lds_bytes<BF, 1>(), s>>>(a, RG);
+      gemm_staged_kernel<3, AM, EPI, 2>
+          <<<base / 2 * RG, 256, gemm_staged_lds_bytes<3, 2>(), s>>>(a, RG);
+    } else if (g == 3) gemm_staged_kernel<3, AM, EPI><<<base * RG, 256, gemm_staged_lds_bytes<3>(), s>>>(a, RG);
+    else if (g == 2) gemm_staged_kernel<2, AM, EPI><<<base * RG, 256, gemm_staged_lds_bytes<2>(), s>>>(a, RG);
+    else gemm_staged_kernel<1, AM, EPI><<<base * RG, 256, gemm_staged_lds_bytes<1>(), s>>>(a, RG);
     return hipGetLastError();
   }
   const dim3 grid(base), block(256);
   switch (a.MT) {
 #define AS2D_MT(mt) \
-  case mt: gemm_staged_kernel<BF, mt, AM, EPI><<<grid, block, gemm_staged_lds_bytes<BF, mt>(), s>>>(a, 1); break;
+  case mt: gemm_staged_kernel<mt, AM, EPI><<<grid, block, gemm_staged_lds_bytes<mt>(), s>>>(a, 1); break;
     AS2D_MT(3) AS2D_MT(4) AS2D_MT(5) AS2D_MT(6) AS2D_MT(7) AS2D_MT(8) AS2D_MT(9)
 #undef AS2D_MT
     default: return hipErrorInvalidValue;
@@ -311,10 +310,10 @@ hipError_t launch_gemm(bool bf16, int amode, int epi, const GemmArgs& a, hipStre
 // the block to finish (one quarter wave per row and head), else by
 // attn_merge_kernel (one wave per row and head).
 //
-// Prefill passes (one request): one workgroup per (query
+// Prefill passes (one request) of float32 models: one workgroup per (query
 // head, 16 rows) walks the spans in ascending order and merges them as it
-// goes, with the same arithmetic, so no partials go through memory.
-
+// goes, with the same arithmetic, so no partials go through memory
+// (attn_prefill.hip does so for bf16 models).
 
 // The items of a launch with blocks of RT row tiles.  LOWREG (RT = 1): a
 // workgroup within half the register file (two per compute unit), one span
@@ -457,7 +456,8 @@ __global__ __launch_bounds__(64) void attn_merge_kernel(const AttnArgs p, int n_
   attn_merge_wave<BF, D>(p, rq, i, u - i * p.n_q);
 }
 
-// Prefill attention: one workgroup per (query head, 16-row tile) runs
+// Prefill attention of float32 models (bf16: attn_prefill.hip): one workgroup
+// per (query head, 16-row tile) runs
 // the tile's spans two at a time with eight waves, group 0 (waves 0-3) on
 // spans 0, 2, 4, ..., group 1 on spans 1, 3, 5, ...,
 // each group on its own LDS span buffer and with one chunk buffer in
@@ -468,13 +468,14 @@ __global__ __launch_bounds__(64) void attn_merge_kernel(const AttnArgs p, int n_
 // group 1's state handed over through the LDS; the same arithmetic as one
 // span at a time.  Group 1 runs the last span again when the count is odd
 // (its state is not merged) so that both groups reach the same barriers.
-template <bool BF, int D> __host__ __device__ constexpr int attn_prefill_lds_bytes() {
-  return 2 * attn_span_lds_bytes<BF, D, 1>() + kWaves * (2 + D / 64) * 64 * 16;
+template <int D> __host__ __device__ constexpr int attn_prefill_lds_bytes() {
+  return 2 * attn_span_lds_bytes<false, D, 1>() + kWaves * (2 + D / 64) * 64 * 16;
 }
 
-template <bool BF, int D>
+template <int D>
 __global__ __launch_bounds__(512) void attn_prefill_kernel(const AttnArgs p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  constexpr bool BF = false;
   constexpr int KS = D / AttnFmt<BF>::KE;
   constexpr int DTW = D / 64;
   const int h = blockIdx.x, r0 = blockIdx.y * 16;
@@ -549,7 +550,7 @@ static hipError_t attn_dispatch(const AttnArgs& a, int n_reqs, int max_blocks, b
   if (prefill) {
     if (n_reqs != 1) return hipErrorInvalidValue;
     if constexpr (BF) return launch_attn_prefill(a, s);
-    else attn_prefill_kernel<BF, D><<<dim3(a.n_q, (a.M + 15) / 16), 512, attn_prefill_lds_bytes<BF, D>(), s>>>(a);
+    else attn_prefill_kernel<D><<<dim3(a.n_q, (a.M + 15) / 16), 512, attn_prefill_lds_bytes<D>(), s>>>(a);
     return hipGetLastError();
   }
   // items of one-tile blocks at the slot capacity, from the most rows a
@@ -601,7 +602,7 @@ static hipError_t prepare_staged() {
     if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
   };
 #define AS2D_S(mt) \
-  allow(reinterpret_cast<const void*>(&gemm_staged_kernel<false, mt, AM, EPI>), gemm_staged_lds_bytes<false, mt>());
+  allow(reinterpret_cast<const void*>(&gemm_staged_kernel<mt, AM, EPI>), gemm_staged_lds_bytes<mt>());
   AS2D_S(1) AS2D_S(2) AS2D_S(3) AS2D_S(4) AS2D_S(5) AS2D_S(6) AS2D_S(7) AS2D_S(8) AS2D_S(9)
 #undef AS2D_S
   return e;
@@ -616,7 +617,7 @@ static hipError_t prepare_attention() {
   hipError_t e = allow(reinterpret_cast<const void*>(&attn_group_kernel<BF, D>), attn_span_lds_bytes<BF, D, 2>());
   if constexpr (!BF)
     if (e == hipSuccess)
-      e = allow(reinterpret_cast<const void*>(&attn_prefill_kernel<BF, D>), attn_prefill_lds_bytes<BF, D>());
+      e = allow(reinterpret_cast<const void*>(&attn_prefill_kernel<D>), attn_prefill_lds_bytes<D>());
   return e;
 }
 

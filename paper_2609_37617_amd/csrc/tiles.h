@@ -1126,10 +1126,10 @@ __device__ __forceinline__ void gemm_range_direct_ra(const GemmArgs& p, int M, u
 // (default: the pair group).
 // WC: weight tiles by ordinary cached loads (the other row groups of the
 // pass read them again from L2), else by streaming loads.
-//   smem: dynamic LDS of gemm_staged_lds_bytes<BF, MT, NPW>().
+//   smem: dynamic LDS of gemm_staged_lds_bytes<MT, NPW>().
 
-template <bool BF, int MT> __host__ __device__ constexpr int staged_ck() {
-  constexpr int per = 2 * (BF ? 2 : 1) * MT * 1024;   // both buffers, one k-step
+template <int MT> __host__ __device__ constexpr int staged_ck() {
+  constexpr int per = 2 * MT * 1024;   // both buffers, one k-step
   constexpr int cap = MT == 2 || MT == 3 ? 2 : 4;     // row groups of 2-3 tiles: few enough registers for 4 workgroups per CU
   return kStagedLds / per > cap ? cap : kStagedLds / per;
 }
@@ -1137,19 +1137,18 @@ template <bool BF, int MT> __host__ __device__ constexpr int staged_ck() {
 // (floats) and rows per pass (at most the workgroup's rows).
 template <int NPW> __host__ __device__ constexpr int staged_fstride() { return kPairsS * NPW * kPairCols + 4; }
 template <int MT> __host__ __device__ constexpr int staged_frows() { return MT * 16 < kFRows ? MT * 16 : kFRows; }
-template <bool BF, int MT, int NPW = 1> __host__ __device__ constexpr int gemm_staged_lds_bytes() {
-  constexpr int a = 2 * (BF ? 2 : 1) * MT * staged_ck<BF, MT>() * 1024;
+template <int MT, int NPW = 1> __host__ __device__ constexpr int gemm_staged_lds_bytes() {
+  constexpr int a = 2 * MT * staged_ck<MT>() * 1024;
   constexpr int f = staged_frows<MT>() * staged_fstride<NPW>() * 4;
   return a > f ? a : f;
 }
 
-template <bool BF, int MT, int AM, int EPI, bool COH, bool WC = false, int NPW = 1>
+template <int MT, int AM, int EPI, bool WC, int NPW>
 __device__ bool gemm_tile_staged(const GemmArgs& p, int M, int group, int split, unsigned char* smem,
-                                 float* s_scale, int* s_flag, int mt0 = 0, int cnt = -1) {
-  constexpr int kRegions = BF ? 2 : 1;
+                                 float* s_scale, int* s_flag, int mt0, int cnt) {
   constexpr int PG = kPairsS * NPW;                // pairs of the workgroup, NPW per wave
-  constexpr int CK = staged_ck<BF, MT>();
-  constexpr int BUF = kRegions * MT * CK * 64;     // 16-byte elements per buffer
+  constexpr int CK = staged_ck<MT>();
+  constexpr int BUF = MT * CK * 64;     // 16-byte elements per buffer
   constexpr int NV = (BUF + 255) / 256;            // of which each thread stages at most NV
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int kt0 = split * p.ktps;
@@ -1157,8 +1156,7 @@ __device__ bool gemm_tile_staged(const GemmArgs& p, int M, int group, int split,
   const size_t pstride = (size_t)p.KT * 128;                                   // 16-byte units per pair
   const uint4* wp = p.W + (size_t)(group * PG + wave * NPW) * pstride + lane;   // this wave's first pair
   const uint4* ag = static_cast<const uint4*>(p.A);
-  const long long lo = p.a_plane / ET<BF>::PER16;
-  uint4* la = reinterpret_cast<uint4*>(smem);     // [buffer][region][mt][k-step of chunk][lane]
+  uint4* la = reinterpret_cast<uint4*>(smem);     // [buffer][mt][k-step of chunk][lane]
 
   // chunk (slice q, first k-step c0, n k-steps); q == ns: past the end
   struct Chunk {
@@ -1181,7 +1179,7 @@ __device__ bool gemm_tile_staged(const GemmArgs& p, int M, int group, int split,
     }
     return first_of(c.q + 1);
   };
-  // element u of chunk d's staging: block (region, tile, k-step) u / 64,
+  // element u of chunk d's staging: block (tile, k-step) u / 64,
   // position u % 64 of the block in LDS, which holds the 16-byte unit lane
   // u % 64 feeds to the MFMA (frag_lane_unit): the waves then read their
   // fragments as 64 consecutive units, free of bank conflicts (read in
@@ -1192,10 +1190,9 @@ __device__ bool gemm_tile_staged(const GemmArgs& p, int M, int group, int split,
   const int mt_last = (M - 1) >> 4;
   auto elem = [&](const Chunk& d, int u, int& dst) {
     const int pos = u & 63, b = u >> 6;
-    const int rg = b / (MT * d.n), r2 = b - rg * (MT * d.n);
-    const int mt = r2 / d.n, r = r2 - mt * d.n;
-    dst = ((rg * MT + mt) * CK + r) * 64 + pos;
-    return ag + rg * lo + ((size_t)min(mt0 + mt, mt_last) * p.KT + d.c0 + r) * 64 + frag_lane_unit(pos);
+    const int mt = b / d.n, r = b - mt * d.n;
+    dst = (mt * CK + r) * 64 + pos;
+    return ag + ((size_t)min(mt0 + mt, mt_last) * p.KT + d.c0 + r) * 64 + frag_lane_unit(pos);
   };
   // requests chunk d: CK k-steps of weights (past the chunk its last
   // again, clamped to the matrix: unused) and this thread's NV staging
@@ -1216,12 +1213,12 @@ __device__ bool gemm_tile_staged(const GemmArgs& p, int M, int group, int split,
         }
       }
     }
-    const int total = max(kRegions * MT * d.n * 64, 1);
+    const int total = max(MT * d.n * 64, 1);
 #pragma unroll
     for (int i = 0; i < NV; ++i) av[i] = ldg(elem(d, min((int)tid + 256 * i, total - 1), ad[i]));
   };
   auto stage = [&](const Chunk& d, uint4* buf, const uint4(&av)[NV], const int(&ad)[NV]) {
-    const int total = kRegions * MT * d.n * 64;
+    const int total = MT * d.n * 64;
 #pragma unroll
     for (int i = 0; i < NV; ++i)
       if ((int)tid + 256 * i < total) buf[ad[i]] = av[i];
@@ -1256,11 +1253,10 @@ __device__ bool gemm_tile_staged(const GemmArgs& p, int M, int group, int split,
         for (int mt = 0; mt < MT; ++mt) {
           AFrag af;
           af.h = lb[(mt * CK + ks) * 64 + lane];
-          if constexpr (BF) af.l = lb[MT * CK * 64 + (mt * CK + ks) * 64 + lane];
 #pragma unroll
           for (int q = 0; q < NPW; ++q) {
-            acc[mt][q][0] = mma_a<BF>(af, wc[ks][q][0], acc[mt][q][0]);
-            acc[mt][q][1] = mma_a<BF>(af, wc[ks][q][1], acc[mt][q][1]);
+            acc[mt][q][0] = mma_a<false>(af, wc[ks][q][0], acc[mt][q][0]);
+            acc[mt][q][1] = mma_a<false>(af, wc[ks][q][1], acc[mt][q][1]);
           }
         }
       }
@@ -1294,7 +1290,6 @@ __device__ bool gemm_tile_staged(const GemmArgs& p, int M, int group, int split,
   constexpr int FS = staged_fstride<NPW>(), FR = staged_frows<MT>();
   const int n0 = group * PG * kPairCols, C = PG * kPairCols;
   const int R0 = mt0 * 16, R1 = min(M, (mt0 + MT) * 16);   // this workgroup's rows
-  if (cnt < 0) cnt = group;
   // lane's value of (row m, column 32 (NPW wave + q) + 16 j + lane % 16)
   auto put = [&](int r0, int r1, bool scale) {
 #pragma unroll
@@ -1335,7 +1330,7 @@ __device__ bool gemm_tile_staged(const GemmArgs& p, int M, int group, int split,
       const int r1 = min(R1, r0 + FR);
       fixup_rows<AM>(p, M, n0, C, r0, r1, s_scale, F, FS);
       lds_sync();
-      epilogue_rows<BF, EPI, COH>(p, F, FS, group * PG, PG, r0, r1);
+      epilogue_rows<false, EPI, false>(p, F, FS, group * PG, PG, r0, r1);
       lds_sync();
     }
   } else {
@@ -1345,7 +1340,7 @@ __device__ bool gemm_tile_staged(const GemmArgs& p, int M, int group, int split,
       const int r1 = min(R1, r0 + FR);
       put(r0, r1, true);
       lds_sync();
-      epilogue_rows<BF, EPI, COH>(p, F, FS, group * PG, PG, r0, r1);
+      epilogue_rows<false, EPI, false>(p, F, FS, group * PG, PG, r0, r1);
       lds_sync();
     }
   }
