@@ -9,8 +9,9 @@ outnumber its grid.  Every combination must reach the result of the others
 bit for bit (logits, outcome and the appended KV): 7B shape, two layers, one
 request verifying k = 8 after a prefix of 900 tokens (8 spans of one-tile
 blocks, one workgroup each: in a 1,024-key slot merged by the last item, in
-an 8,192-key slot by the merge kernel) and of 4,500 tokens (36 spans: runs
-of two spans with two-tile blocks, of three with one-tile blocks).
+an 8,192-key slot by the merge kernel) and of 4,500 tokens (36 spans: a row
+tile per wave as the launch chooses, against blocks whose waves share a tile:
+runs of two spans with two-tile blocks, of three with one-tile blocks).
 """
 import os
 

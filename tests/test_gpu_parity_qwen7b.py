@@ -7,7 +7,7 @@ against the float64 oracle on the same seeded inputs, for
   {0, 1, 2, 4, 8, 16} and p in {0.1, 0.3, 0.6};
 * the long-audio workload (7,500 + 64 prefix rows, k = 8, p = 0.4);
 * the mixed batch: all sixteen requests verified in fused passes (68 rows,
-  the staged GEMM path), two of them against the oracle;
+  the wide GEMM tiles), two of them against the oracle;
 
 plus the bitwise properties of the full-depth GPU model itself: batched
 verification equals sequential decoding (Appendix C.4, requirement 1), a
@@ -224,7 +224,7 @@ def test_qwen7b_mixed_batch(m7):
         for i in ids:
             done[i] += outs[i]["accepted_len"] + 1
         log(f"[7B mixed batch] round {rnd}: {rows} rows in the fused pass")
-    assert rows > 32               # the staged GEMM path
+    assert rows > 32               # the wide GEMM tiles
     for i in oms:
         compare_kv(oms[i], gpu, i, 0, oms[i].kv_len, KV_TOL)
         compare_kv(oms[i], gpu, i, LAST, oms[i].kv_len, KV_TOL)

@@ -1,31 +1,37 @@
-"""A prefilled cache equals the incrementally built one bit for bit at the 7B
-widths, with prefixes of several spans.
+"""A prefilled cache equals the incrementally built one bit for bit, with
+prefixes of several spans.
 
 Commit-and-repair (Appendix C.4): after verification rounds with rejections,
 a fresh prefill of the committed prefix must reproduce the retained cache.
-Prefill attention runs its spans two at a time (two groups of four waves, the
-second handing its span state to the first) while verification stores every
-span's state and merges them in order; both must reach the same bits. The
-second layer's keys and values depend on the first layer's attention output,
-so they compare the two attention paths. Prefixes of 256 and 300 rows (two
-and three spans) are extended by the verification rounds and prefilled again
-in two passes of at most 144 rows, so the row tiles see even and odd span
-counts, and one whose last span is the group-1 span run again.
+The second layer's keys and values depend on the first layer's attention
+output, so they compare the two attention paths: verification stores every
+span's state and merges them in order; a bf16 prefill (7B shape) walks all
+spans chunk by chunk in one pass; a float32 prefill (3B and 0.5B widths, for
+both head sizes) runs its spans two at a time, the second group of four waves
+handing its span state to the first, in passes of at most 144 rows. Prefixes
+of 256 and 300 rows (two and three spans) are extended by the verification
+rounds and prefilled again, so the row tiles see even and odd span counts,
+and one whose last span is the second group's span run again.
 """
+from dataclasses import replace
+
 import numpy as np
 import pytest
 
 from tests.harness import make_pair, prefix
-from workload import QWEN7B
+from workload import QWEN3B, QWEN7B, QWEN05B
+from workload.configs import F32
 
 pytestmark = pytest.mark.gpu
 
-SHAPE = QWEN7B.with_layers(2)
+SHAPES = [QWEN7B.with_layers(2)] + [replace(s.with_layers(2), name=s.name + "-f32", dtype=F32, vocab=4096)
+                                    for s in (QWEN3B, QWEN05B)]
 
 
+@pytest.mark.parametrize("SHAPE", SHAPES, ids=lambda s: s.name)
 @pytest.mark.parametrize("n_audio,n_instr", [(240, 16), (284, 16)])
-def test_prefill_equals_incremental_several_spans(n_audio, n_instr):
-    print(f"7B shape, 2 layers, prefix {n_audio} + {n_instr}", flush=True)
+def test_prefill_equals_incremental_several_spans(SHAPE, n_audio, n_instr):
+    print(f"{SHAPE.name}, prefix {n_audio} + {n_instr}", flush=True)
     _, gpu = make_pair(SHAPE, seed=11, max_requests=2, max_kv_len=1024, max_k=8, oracle=False)
     try:
         _, a_dev, instr = prefix(SHAPE, n_audio, n_instr, 11, 0)

@@ -69,21 +69,25 @@ def test_short_memory_shrinks_the_passes():
     loads with smaller passes.  7B attention widths and a wide MLP, one layer:
     0.8 GB of weights (1.3 GB while they are packed) and 0.2 GB of other
     buffers, 1.7 GB for passes of 8,192 rows; 2 GB are left free."""
-    import torch
+    import ctypes
+    from paper_2609_37617_amd import as2d
     shape = replace(QWEN7B.with_layers(1), name="wide-mlp", ffn=32768, vocab=4096)
     ensure_built()
     weights = gen.make_weights(shape, 5, fmt="device")
     ref = run(shape, weights, 8000, 8192, 1)
-    torch.cuda.synchronize()
-    hold, left = [], 2 * 10 ** 9
-    for _ in range(4):
-        free = torch.cuda.mem_get_info()[0]
-        if free - left > 64 << 20:
-            hold.append(torch.empty(free - left, dtype=torch.uint8, device="cuda"))
-    print(f"{torch.cuda.mem_get_info()[0] / 1e9:.2f} GB free", flush=True)
+    hip = as2d.load_library()   # its HIP runtime
+    left, held = 2 * 10 ** 9, []
+    free, total = ctypes.c_size_t(), ctypes.c_size_t()
     try:
+        for _ in range(4):
+            assert hip.hipMemGetInfo(ctypes.byref(free), ctypes.byref(total)) == 0
+            if free.value - left > 64 << 20:
+                p = ctypes.c_void_p()
+                assert hip.hipMalloc(ctypes.byref(p), ctypes.c_size_t(free.value - left)) == 0
+                held.append(p)
+        print(f"{free.value / 1e9:.2f} of {total.value / 1e9:.2f} GB free", flush=True)
         got = run(shape, weights, 8000, 8192, 1)
     finally:
-        del hold
-        torch.cuda.empty_cache()
+        for p in held:
+            hip.hipFree(p)
     check_same(got, ref)

@@ -1,24 +1,29 @@
-"""Prefill through the staged GEMMs gives the same bits whatever the row
-grouping: groups of 3 row tiles with two tile pairs per wave on every
-matrix, a mix of 3 tiles for gate/up, 2 for QKV and 1 for O and down, the
-default (3 tiles for gate/up, 1 elsewhere), and single-tile groups
-everywhere.  Row grouping only changes which
-workgroup computes which rows, never the order of a sum.  7B shape, two
-layers (the second layer's KV depends on every GEMM of the first), the
-782-row prefix (passes of 144 rows and one of 62); compares both layers'
-KV, the first token and the logits of one decode step after the prefill."""
+"""Prefill through the staged GEMMs (float32 models, passes of more than 32
+rows) gives the same bits whatever the row grouping: groups of 3 row tiles
+with two tile pairs per wave on every matrix but gate/up (whose workgroups
+take all rows), groups of 2 for O, the default (3 for QKV and down, single
+tiles for O, and single tiles everywhere in the short pass), and single tiles
+everywhere.  Row grouping only changes which workgroup computes which rows,
+never the order of a sum.  7B widths in float32, two layers (the second
+layer's KV depends on every GEMM of the first), the 782-row prefix (passes of
+144 rows and one of 62); compares both layers' KV, the first token and the
+logits of one decode step after the prefill.  The 0.5B widths, whose gate/up
+is grouped too: test_gpu_rowgroups_f32.py."""
+from dataclasses import replace
+
 import numpy as np
 import pytest
 
 from tests.harness import ensure_built, prefix
 from workload import QWEN7B, gen
+from workload.configs import F32
 
 pytestmark = pytest.mark.gpu
 
-SHAPE = QWEN7B.with_layers(2)
-# least grid for row groups of 2-3 tiles: 0 -> always 3 tiles; 448 -> groups
-# of 2 for QKV; 700 -> the library's default; 1e5 -> always 1 tile
-SETTINGS = (0, 448, 700, 100000)
+SHAPE = replace(QWEN7B.with_layers(2), name="7b-widths-f32", dtype=F32, vocab=4096)
+# least grid for row groups of 2-3 tiles: 0 -> always 3 tiles; 250 -> groups
+# of 2 for O; 700 -> the library's default; 1e5 -> always 1 tile
+SETTINGS = (0, 250, 700, 100000)
 
 
 @pytest.fixture(scope="module")

@@ -1,7 +1,8 @@
 """The wide GEMM path (prefill passes of more than 32 rows) gives the bits of
 the one-row path: a reply is decoded one token at a time, then its prefix is
-prefilled afresh at lengths around the tiles' and passes' edges; every key
-and value and the next token must be the same."""
+prefilled afresh, each time in one pass, at lengths around the tiles' edges;
+every key and value and the next token must be the same.  (Several passes:
+test_gpu_prefill_passes.py.)"""
 from dataclasses import replace
 
 import numpy as np
@@ -13,7 +14,7 @@ from workload import QWEN3B, QWEN7B, QWEN05B, TINY_BF16
 pytestmark = pytest.mark.gpu
 
 # 16-row tiles 3 and up, tile heights of 2, 3 and 4 row tiles and one row more,
-# a whole pass (2,048 rows) and two passes
+# and passes of many row blocks, whole (2,048 rows) and ragged
 LENGTHS = (33, 48, 49, 64, 65, 97, 128, 129, 193, 290, 511, 782, 1297, 2048, 2060)
 
 

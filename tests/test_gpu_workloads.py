@@ -6,7 +6,7 @@ workloads' real prefix lengths and request mix:
   and p = 0.4; the attention spans 237 key chunks;
 * mixed batch: the sixteen requests of the batch workload (ragged
   prefixes of 282..3032 rows, k in {0, 4, 8}) verified in fused passes of
-  up to 144 rows (the staged GEMM path); a sample of the requests is
+  up to 144 rows (the wide GEMM tiles); a sample of the requests is
   checked against the oracle, and every request's result in the fused pass
   must equal, bit for bit, the same request verified alone (the direct
   GEMM path), which is the batch-invariance property at full width."""
@@ -119,7 +119,7 @@ def test_qwen7b_mixed_batch_width():
             assert gpu.state(i) == after[i]
         for i in ids:
             done[i] += outs[i]["accepted_len"] + 1
-    assert rows_max > 32, rows_max    # the fused passes took the staged path
+    assert rows_max > 32, rows_max    # the fused passes took the wide tiles
     for i in oms:
         compare_kv(oms[i], gpu, i, 0, oms[i].kv_len, 2e-3)
     print(f"mixed batch: rounds={st.rounds} committed={st.committed} near_ties={st.near_ties} "
