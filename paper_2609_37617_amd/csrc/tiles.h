@@ -606,7 +606,8 @@ template <bool BF> inline constexpr int kRangeSL[3] = {2, 16, 28};
 template <> inline constexpr int kRangeSL<false>[3] = {4, 4, 4};
 
 // The balanced path takes the register-resident variant for KS = 1 and a
-// slice length from kRangeSL, for the gate/up and LM-head products
+// slice length from kRangeSL (hidden 256, 2,048 and 3,584 in bf16, 256 in
+// float32; other widths stream their activations), for the gate/up and LM-head products
 // (normalised A; a workgroup has several pairs): its slice length, else 0.
 // Two row tiles only for bf16 models.
 template <bool BF>
@@ -1034,7 +1035,8 @@ __device__ __forceinline__ void gemm_range_direct(const GemmArgs& p, int M, unsi
 // (256 registers); of a longer one the first tile is held and the second
 // streams with the weights, which halves the activation reads: they, not
 // the weights, bound two row tiles (2 KiB of weights against 4 KiB of
-// fragments per k-step of a pair).  Gate/up against gemm_range_direct, back
+// fragments per k-step of a pair); the 28-step slice then fills all 512
+// registers and spills 9 (40 bytes per lane).  Gate/up against gemm_range_direct, back
 // to back, 7B shape: 17 rows 58.3 -> 52.2 us, 24 65.2 -> 53.6, 32
 // 72.6 -> 60.6 (9 rows: 47.3); 3B: 25.4 -> 23.4, 27.6 -> 24.5,
 // 30.1 -> 26.0.  Sums as in gemm_range_direct.

@@ -26,7 +26,8 @@
 // workgroups per compute unit (4 x 4 tiles: 1.1 PFLOP/s of (hi, lo) products
 // at 1,904 rows, about the rate of a plain 8192^3 library product on this
 // device; one workgroup of 8 x 4 tiles per unit, with half the reads per
-// product, reached 0.7).  782 rows of the 7B shape, against passes of 144
+// product, reached 0.7).  The 4 x 4 tiles fill the 256 registers that two
+// workgroups leave them and spill 4 to 6 (20 to 28 bytes per lane).  782 rows of the 7B shape, against passes of 144
 // rows through the staged path it replaces: gate/up 780 -> 432 us, down
 // 640 -> 240, QKV 354 -> 88, O 198 -> 69 us; at 84 rows (a fused batch)
 // 115 -> 90, 106 -> 61, 48 -> 27, 33 -> 21 us.  (QKV and O were 77 and 55,
